@@ -85,15 +85,19 @@ enum dirac_status {
  * steps and the conserved functional, instead of wrapping periodically.  The
  * summation by parts in the proofs of the Lemmas (Sect. 2, Sect. 3) leaves no
  * boundary terms with zero values outside either, so E_r stays exactly
- * conserved.  Steps run on the split kernels (one launch per half-step, in
- * place).  Not combined with DIRAC_SLAB_Z (DIRAC_E_ARG); dirac_set_links and
+ * conserved.  3D steps run on the split kernels (one launch per half-step, in
+ * place); 2D ones on register tiles (below) in an even number of passes, so the
+ * state stays in its buffer set, or in place where the two sets share an array.
+ * Not combined with DIRAC_SLAB_Z (DIRAC_E_ARG); dirac_set_links and
  * dirac_adjoint_vz are refused (DIRAC_E_STATE).
  */
 #define DIRAC_ZERO_BC 4u
 
 /* step kernels (dirac_set_kernel) */
 enum dirac_kernel {
-    DIRAC_KERNEL_AUTO = 0,   /* FUSED2 where it applies, else FUSED                */
+    DIRAC_KERNEL_AUTO = 0,   /* 3D: FUSED2 where it applies, else FUSED; 2D: register
+                                tiles, up to 8 steps per launch, ping-pong, as many
+                                launches (mod 2) as FUSED2 / FUSED would make       */
     DIRAC_KERNEL_SPLIT = 1,  /* one launch per half-step, in place                 */
     DIRAC_KERNEL_FUSED = 2,  /* one launch per step, ping-pong between the buffers */
     DIRAC_KERNEL_FUSED2 = 3  /* one launch per two steps (3D: V(z) tables or
@@ -296,8 +300,8 @@ int dirac_coef_from_fields(void *coef, int dtype, double dt, double sgn_m, const
  *           kernels (default: chosen per kernel and lattice from the number of
  *           workgroups the device runs at once and each chunk's pipeline fill)
  * The two-step kernel uses 64 x 8 tiles (complex64) or 32 x 8 (complex128).
- * Every kernel gives the same bits.  The reversed step always uses the split
- * kernels, the adjoint its own in-place sweeps. */
+ * Every kernel gives the same bits.  In 2D a zchunk takes the march kernels.  The
+ * adjoint uses its own in-place sweeps. */
 int dirac_set_kernel(dirac_ctx *ctx, int kernel, int tile_y, int zchunk);
 
 /*
@@ -453,9 +457,11 @@ int dirac_batch_bind(dirac_ctx *ctx, void *const state[], void *const partner[],
  * Advance every lattice by n steps.  mode 0: one persistent launch for all n
  * steps with a per-lattice barrier between passes; mode 1: one launch per pass
  * over all lattices (both replayed from a captured HIP graph when use_graph !=
- * 0).  A pass advances one step or, with the tuned tile candidate's two-step
- * march (even nx for complex64), two; an odd remainder takes one one-step pass.
- * After an odd n the partner buffers hold the state (dirac_current).  Mode 0
+ * 0).  In mode 1, unless the tuner chose otherwise, a pass advances up to 8 steps
+ * on register tiles; with a tuned march candidate, and in mode 0, one step or,
+ * with a two-step march (even nx for complex64), two, an odd remainder then
+ * taking one one-step pass.  dirac_current tells which buffers hold the state;
+ * untuned, the ones that two-step marches would leave it in.  Mode 0
  * needs its whole grid resident at once: the first mode-0 call for a kernel in
  * a process measures that grid by census-only launches (synchronous; no state
  * touched), and every persistent launch opens with a census that leaves
@@ -472,8 +478,9 @@ int dirac_batch_run(dirac_ctx *ctx, int64_t n, int mode, int use_graph, void *st
 int dirac_batch_norms(dirac_ctx *ctx, double *out, void *stream);
 
 /*
- * Pick the batched kernel's tile shape (x strip width, y chunk height) for
- * each mode by timing every candidate for a few steps on the bound lattices.
+ * Pick the batched kernel's tile shape (x strip width, y chunk height, or in
+ * mode 1 the register tiles) for each mode by timing every candidate for a few
+ * steps on the bound lattices.
  * This advances the bound state by an even number of steps (it stays in the
  * same buffer set); callers that need the state unchanged save and restore it.
  * If a persistent (mode 0) candidate times out (see dirac_batch_run) it is

@@ -1,9 +1,10 @@
 // Batched (2+1)D lattices: many independent lattices of different sizes,
 // masses and potentials (per-site theta) advanced together.
 //
-// Work is a flat list of items (lattice, x strip, y chunk); each item is one
-// workgroup's fused (2+1)D pass over its strip and chunk: one step (march2.h)
-// or two (march2x2.h), per the tuning candidate.
+// Work is a flat list of items.  By default in mode 1 an item is one register
+// tile of a lattice (tile2.h), which a pass advances several steps; the tuning
+// candidates' items are (lattice, x strip, y chunk), each one workgroup's fused
+// (2+1)D pass over its strip and chunk: one step (march2.h) or two (march2x2.h).
 //  mode 1: one launch per pass over all items of all lattices;
 //  mode 0: one persistent launch for all steps, in passes of one step or (the
 //          two-step candidates) two steps, an odd remainder then taking one
@@ -40,6 +41,8 @@
 #include "internal.h"
 #include "march2.h"
 #include "march2x2.h"
+#include "tile2.h"
+#include "tile2_plan.h"
 
 using namespace dirac;
 
@@ -66,6 +69,10 @@ const Cand kCands[] = {{64, 16, 1},  {64, 32, 1},  {128, 16, 1}, {128, 32, 1}, {
                        {256, 32, 2}, {256, 64, 2}, {256, 128, 2}};
 constexpr int kNumCands = (int)(sizeof(kCands) / sizeof(kCands[0]));
 constexpr int kDefaultCand = 10;
+// The choice number of the register tile (mode 1 only; its shape and steps per
+// pass follow from the lattices and the number of steps).  Last, so that choices
+// kept in cache files mean what they meant.
+constexpr int kTileCand = kNumCands;
 constexpr long kSpinLimit = 1L << 22;
 // counter words of a persistent launch after the per-lattice ones: the abort
 // flag, the census word and the census's closing count
@@ -146,6 +153,8 @@ __device__ __forceinline__ FusedArgs<R> item_args(const BatchLat &L, int parity,
     a.npart = nullptr;
     a.npart_cap = 0;
     a.zh = 0;
+    a.px = 0;
+    a.rev = 0;
     return a;
 }
 
@@ -179,6 +188,28 @@ __global__ __launch_bounds__(TW + 64) void kb_step2(const BatchLat *lats, const 
     const BatchLat &L = lats[w.lat];
     FusedArgs<R> a = item_args<R>(L, parity, ly);
     march2x2<R, true, TW>(a, nullptr, w.tx, w.yc, sOld, sStage, sLev);
+}
+
+// Several steps per launch on register tiles: block b is tile b - item0 of the
+// lattice whose tiles contain it.  The lattice is found by the whole wave at
+// once, 64 item0 per look: one look for up to 64 lattices, two for 4096.
+template <typename R, int K, int NW>
+__global__ __launch_bounds__(NW * 64, 4) void kb_tile(const BatchLat *lats, int count, int steps, int ring,
+                                                      int parity) {
+    __shared__ T2Edge<R, NW> sh;
+    const int b = item_of_block(blockIdx.x, gridDim.x), lane = threadIdx.x & 63;
+    int lo = 0, len = count;
+    while (len > 1) {
+        const int step = (len + 63) / 64, at = lane * step;
+        const bool le = at < len && lats[lo + (at < len ? at : 0)].item0 <= b;
+        const int k = __popcll(__ballot(le)) - 1;
+        len = min(step, len - k * step);
+        lo += k * step;
+    }
+    const BatchLat &L = lats[__builtin_amdgcn_readfirstlane(lo)];
+    FusedArgs<R> a = item_args<R>(L, parity, 0);
+    const int t = b - L.item0, tw = 64 - 2 * ring, ntx = (L.nx + tw - 1) / tw;
+    tile2<R, true, false, K, NW>(a, nullptr, steps, ring, t % ntx, t / ntx, sh);
 }
 
 // Per-lattice step barrier of the persistent launches: before pass s of an
@@ -385,10 +416,42 @@ void resident_forget(bool fp32, int txb, bool two) {
     std::lock_guard<std::mutex> lk(g_resident_mu);
     g_resident.erase(resident_key(fp32, txb, two));
 }
-// Upload lattice descriptors and the item list of candidate q.
-int upload_batch(dirac_ctx *c, int q, hipStream_t s, int64_t *nitems_out) {
+// Two-step marches move whole rows in 16-byte units with a per-unit x wrap,
+// which needs an even row length for complex64: otherwise one-step passes.
+bool two_step_ok(const dirac_ctx *c) {
+    if (c->dtype != DIRAC_C64) return true;
+    for (int64_t b = 0; b < c->count; ++b)
+        if (c->bnx[(size_t)b] % 2 != 0) return false;
+    return true;
+}
+
+// What a run of n steps by choice q launches: the item count and, for the
+// register tile, its passes, shape and ring.
+struct BRun {
+    int q;
+    int64_t nitems, passes;
+    int shape, ring;
+};
+
+// The tile passes of n steps leave the state in the set where two-step marches
+// (one-step ones where they do not apply) would: the same parity of launches.
+void plan_tiles(const dirac_ctx *c, int64_t n, BRun *r) {
+    const bool fp32 = c->dtype == DIRAC_C64;
+    const int64_t flips = two_step_ok(c) ? n / 2 + (n & 1) : n;
+    r->passes = tile2_passes(n, (int)(flips & 1), c->count, c->bnx.data(), c->bny.data(), fp32, true);
+    r->ring = r->passes > 0 ? (int)((n + r->passes - 1) / r->passes) : 1;
+    double us = 0.0;
+    r->shape = tile2_best_shape(r->ring, c->count, c->bnx.data(), c->bny.data(), fp32, true, &us);
+}
+
+// Upload lattice descriptors and the item list of choice q for n steps.
+int upload_batch(dirac_ctx *c, int q, int64_t n, hipStream_t s, BRun *run) {
     const BLayout Ly = blayout(c);
-    const Cand k = kCands[q];
+    const bool tile = q == kTileCand;
+    const Cand k = kCands[tile ? kDefaultCand : q];
+    *run = BRun{q, 0, 0, 0, 0};
+    if (tile) plan_tiles(c, n, run);
+    int64_t tiles = 0;
     std::vector<BatchLat> lats((size_t)c->count);
     std::vector<BatchItem> items;
     for (int64_t b = 0; b < c->count; ++b) {
@@ -401,6 +464,13 @@ int upload_batch(dirac_ctx *c, int q, hipStream_t s, int64_t *nitems_out) {
         L.r = c->bdt[(size_t)b];
         L.nx = (int)c->bnx[(size_t)b];
         L.ny = (int)c->bny[(size_t)b];
+        if (tile) {
+            L.item0 = (int)tiles;
+            tiles += tile2_tiles(run->shape, run->ring, L.nx, L.ny);
+            if (tiles > 0x7fffffff) return bfail(c, DIRAC_E_SHAPE, "too many tiles");
+            L.nitems = (int)(tiles - L.item0);
+            continue;
+        }
         L.item0 = (int)items.size();
         const int ntx = (L.nx + k.txb - 1) / k.txb, nyc = (L.ny + k.ly - 1) / k.ly;
         for (int yc = 0; yc < nyc; ++yc)
@@ -409,15 +479,14 @@ int upload_batch(dirac_ctx *c, int q, hipStream_t s, int64_t *nitems_out) {
     }
     char *base = (char *)c->scratch;
     BCHK(c, hipMemcpyAsync(base + Ly.lats, lats.data(), lats.size() * sizeof(BatchLat), hipMemcpyHostToDevice, s));
-    BCHK(c, hipMemcpyAsync(base + Ly.items, items.data(), items.size() * sizeof(BatchItem), hipMemcpyHostToDevice,
-                           s));
+    if (!tile)
+        BCHK(c, hipMemcpyAsync(base + Ly.items, items.data(), items.size() * sizeof(BatchItem), hipMemcpyHostToDevice,
+                               s));
     BCHK(c, hipStreamSynchronize(s));
-    *nitems_out = (int64_t)items.size();
+    run->nitems = tile ? tiles : (int64_t)items.size();
     return DIRAC_OK;
 }
 
-// Two-step passes move whole rows in 16-byte units with a per-unit x wrap,
-// which needs an even row length for complex64: otherwise one-step passes.
 template <typename R> int calibrate_resident(dirac_ctx *c, int txb, bool two, hipStream_t s, int *grid) {
     if (resident_cached<R>(txb, two, grid) == 0) return DIRAC_OK;
     int g = 0;
@@ -444,28 +513,36 @@ template <typename R> int calibrate_resident(dirac_ctx *c, int txb, bool two, hi
     return bfail(c, DIRAC_E_HIP, "persistent kernel: no co-resident grid found");
 }
 
-bool two_step_ok(const dirac_ctx *c) {
-    if (c->dtype != DIRAC_C64) return true;
-    for (int64_t b = 0; b < c->count; ++b)
-        if (c->bnx[(size_t)b] % 2 != 0) return false;
-    return true;
-}
-
 // Launch n steps starting from buffer set parity0; *flips receives the number
 // of ping-pong launches made (the state ends in set parity0 ^ (flips & 1)).
-template <typename R> int enqueue_run(dirac_ctx *c, int q, int64_t nitems, int64_t n, int mode, int parity0,
-                                      hipStream_t s, int64_t *flips) {
+template <typename R> int enqueue_run(dirac_ctx *c, const BRun &run, int64_t n, int mode, int parity0, hipStream_t s,
+                                      int64_t *flips) {
+    const int64_t nitems = run.nitems;
     const BLayout Ly = blayout(c);
     char *base = (char *)c->scratch;
     const BatchLat *lats = (const BatchLat *)(base + Ly.lats);
     const BatchItem *items = (const BatchItem *)(base + Ly.items);
     unsigned *done = (unsigned *)(base + Ly.done);
-    Cand k = kCands[q];
-    if (k.spp == 2 && !two_step_ok(c)) k.spp = 1;
     *flips = 0;
     if (n == 0) return DIRAC_OK;
     const dim3 g((unsigned)nitems);
     int par = parity0;
+    if (run.q == kTileCand) {
+        const int count = (int)c->count;
+        for (int64_t p = 0; p < run.passes; ++p, par ^= 1, ++*flips) {
+            const int st = (int)(n / run.passes + (p < n % run.passes));
+            if (run.shape == 0)
+                hipLaunchKernelGGL((kb_tile<R, 1, 16>), g, dim3(1024), 0, s, lats, count, st, run.ring, par);
+            else if (run.shape == 1)
+                hipLaunchKernelGGL((kb_tile<R, 2, 16>), g, dim3(1024), 0, s, lats, count, st, run.ring, par);
+            else if constexpr (sizeof(R) == 4)
+                hipLaunchKernelGGL((kb_tile<R, 6, 8>), g, dim3(512), 0, s, lats, count, st, run.ring, par);
+            BCHK(c, hipGetLastError());
+        }
+        return DIRAC_OK;
+    }
+    Cand k = kCands[run.q];
+    if (k.spp == 2 && !two_step_ok(c)) k.spp = 1;
     auto one_step = [&]() -> int {
         if (k.txb == 64) hipLaunchKernelGGL((kb_step<R, 64>), g, dim3(64), 0, s, lats, items, k.ly, par);
         else if (k.txb == 128) hipLaunchKernelGGL((kb_step<R, 128>), g, dim3(128), 0, s, lats, items, k.ly, par);
@@ -523,9 +600,9 @@ template <typename R> int enqueue_run(dirac_ctx *c, int q, int64_t nitems, int64
     return DIRAC_OK;
 }
 
-int enqueue(dirac_ctx *c, int q, int64_t nitems, int64_t n, int mode, int parity0, hipStream_t s, int64_t *flips) {
-    return c->dtype == DIRAC_C64 ? enqueue_run<float>(c, q, nitems, n, mode, parity0, s, flips)
-                                 : enqueue_run<double>(c, q, nitems, n, mode, parity0, s, flips);
+int enqueue(dirac_ctx *c, const BRun &run, int64_t n, int mode, int parity0, hipStream_t s, int64_t *flips) {
+    return c->dtype == DIRAC_C64 ? enqueue_run<float>(c, run, n, mode, parity0, s, flips)
+                                 : enqueue_run<double>(c, run, n, mode, parity0, s, flips);
 }
 
 // The persistent kernel's strip width and steps per pass for candidate q and n steps.
@@ -611,7 +688,7 @@ bool cache_lookup(const char *path, const std::string &key, int out[2]) {
     int a = -1, b = -1;
     if (sscanf(text.c_str() + p, "[%d , %d]", &a, &b) != 2 && sscanf(text.c_str() + p, "[%d,%d]", &a, &b) != 2)
         return false;
-    if (a < 0 || a >= kNumCands || b < 0 || b >= kNumCands) return false;
+    if (a < 0 || a > kTileCand || b < 0 || b >= kNumCands) return false;
     out[0] = a;
     out[1] = b;
     return true;
@@ -723,14 +800,15 @@ int dirac_batch_run(dirac_ctx *c, int64_t n, int mode, int use_graph, void *stre
     if (!c->bound) return bfail(c, DIRAC_E_STATE, "nothing bound (dirac_batch_bind)");
     if (n < 0 || n > (1LL << 30) || (mode != 0 && mode != 1)) return bfail(c, DIRAC_E_ARG, "bad n or mode");
     hipStream_t s = (hipStream_t)stream;
-    const int q = c->tune_choice >= 0 ? (mode == 1 ? (c->tune_choice & 0xff) : (c->tune_choice >> 8)) : kDefaultCand;
+    const int q = c->tune_choice >= 0 ? (mode == 1 ? (c->tune_choice & 0xff) : (c->tune_choice >> 8))
+                                       : (mode == 1 ? kTileCand : kDefaultCand);
     if (!use_graph) {
         drop_graph(c);
-        int64_t nitems = 0;
-        int rc = upload_batch(c, q, s, &nitems);
+        BRun run;
+        int rc = upload_batch(c, q, n, s, &run);
         if (rc) return rc;
         int64_t flips = 0;
-        rc = enqueue(c, q, nitems, n, mode, c->cur, s, &flips);
+        rc = enqueue(c, run, n, mode, c->cur, s, &flips);
         if (rc) return rc;
         if (mode == 0) {
             rc = check_abort(c, q, n, s);
@@ -741,8 +819,9 @@ int dirac_batch_run(dirac_ctx *c, int64_t n, int mode, int use_graph, void *stre
         if (!(c->graph_exec && c->graph_n == n && c->graph_mode == (mode | (q << 4)) && c->graph_cur == c->cur)) {
             drop_graph(c);
             if (!c->graph_stream) BCHK(c, hipStreamCreateWithFlags(&c->graph_stream, hipStreamNonBlocking));
-            int64_t nitems = 0;
-            int rc = upload_batch(c, q, c->graph_stream, &nitems);
+            // on the caller's stream: after the earlier runs that still read the list
+            BRun run;
+            int rc = upload_batch(c, q, n, s, &run);
             if (rc) return rc;
             if (mode == 0) {
                 rc = prepare_mode0(c, q, n, c->graph_stream);
@@ -750,7 +829,7 @@ int dirac_batch_run(dirac_ctx *c, int64_t n, int mode, int use_graph, void *stre
             }
             BCHK(c, hipStreamBeginCapture(c->graph_stream, hipStreamCaptureModeRelaxed));
             int64_t flips = 0;
-            rc = enqueue(c, q, nitems, n, mode, c->cur, c->graph_stream, &flips);
+            rc = enqueue(c, run, n, mode, c->cur, c->graph_stream, &flips);
             c->graph_flips = flips;
             hipGraph_t g = nullptr;
             hipError_t e = hipStreamEndCapture(c->graph_stream, &g);
@@ -831,16 +910,17 @@ int dirac_batch_autotune(dirac_ctx *c, const char *cache_path, int *chosen_out, 
         bool aborted = false;
         for (int mode = 1; mode >= 0; --mode) {
             float best = 1e30f;
-            for (int q = 0; q < kNumCands; ++q) {
-                int64_t nitems = 0;
-                int rc = upload_batch(c, q, s, &nitems);
+            for (int q = 0; q < (mode == 1 ? kNumCands + 1 : kNumCands); ++q) {
+                BRun run;
+                int rc = upload_batch(c, q, timed, s, &run);
                 if (rc) return rc;
                 int64_t flips = 0;
-                rc = enqueue(c, q, nitems, warm, mode, c->cur, s, &flips);
+                // the tile passes' plan is that of `timed` steps
+                rc = enqueue(c, run, q == kTileCand ? timed : warm, mode, c->cur, s, &flips);
                 if (rc) return rc;
                 if (flips & 1) c->cur = 1 - c->cur;
                 BCHK(c, hipEventRecord(e0, s));
-                rc = enqueue(c, q, nitems, timed, mode, c->cur, s, &flips);
+                rc = enqueue(c, run, timed, mode, c->cur, s, &flips);
                 if (rc) return rc;
                 if (flips & 1) c->cur = 1 - c->cur;
                 BCHK(c, hipEventRecord(e1, s));

@@ -13,6 +13,7 @@
 #include "ctx.h"
 #include "gauge.h"
 #include "internal.h"
+#include "tile2_plan.h"
 
 using namespace dirac;
 
@@ -260,6 +261,24 @@ int kernel_choice(const dirac_ctx *c) {
     return DIRAC_KERNEL_FUSED;
 }
 
+// Buffer-set flips of n steps by kernel_choice's kernel: they decide which set
+// ends up with the state.
+int64_t flips_of(const dirac_ctx *c, int64_t n) {
+    const int kc = kernel_choice(c);
+    return kc == DIRAC_KERNEL_SPLIT ? 0 : kc == DIRAC_KERNEL_FUSED2 ? n / 2 + (n & 1) : n;
+}
+
+// (2+1)D with the kernel and its knobs left to the library: several steps per
+// pass on register tiles (tile2.hip).  Not where the two buffer sets share an
+// array, which only the in-place kernels can take.
+bool tile2_applies(const dirac_ctx *c) {
+    if (c->ndim != 2 || c->kernel != DIRAC_KERNEL_AUTO || c->zchunk != 0 || c->links_on) return false;
+    for (int q = 0; q < 4; ++q)
+        for (int p = 0; p < 4; ++p)
+            if (c->buf[0][q] == c->buf[1][p]) return false;
+    return true;
+}
+
 // z-slab mode: the most steps one call may advance between halo refills
 int halo_steps(const dirac_ctx *c) { return kernel_choice(c) == DIRAC_KERNEL_FUSED2 ? 2 : 1; }
 
@@ -318,9 +337,27 @@ template <typename R> int run_reverse_march(dirac_ctx *c, int64_t n, hipStream_t
     return DIRAC_OK;
 }
 
+// n steps on register tiles with `flips` mod 2 buffer-set flips; *done false
+// where there is no such split of n (then nothing was launched).
+template <typename R> int run_tile2(dirac_ctx *c, int64_t n, bool reverse, int64_t flips, hipStream_t s, bool *done) {
+    const int64_t passes = tile2_passes(n, (int)(flips & 1), 1, &c->nx, &c->ny, sizeof(R) == 4, c->site_mode);
+    *done = passes > 0;
+    for (int64_t p = 0; p < passes; ++p) {
+        const FusedArgs<R> a = reverse ? fused_args_rev<R>(c) : fused_args<R>(c);
+        HIPCHK(c, launch_tile2<R>(a, c->site_mode, c->zbc, (int)(n / passes + (p < n % passes)), s));
+        c->cur = 1 - c->cur;
+    }
+    return DIRAC_OK;
+}
+
 template <typename R> int run_steps(dirac_ctx *c, int64_t n, bool reverse, hipStream_t s) {
     int rc = upload_tables(c, s);
     if (rc) return rc;
+    if (tile2_applies(c)) {
+        bool done = false;
+        rc = run_tile2<R>(c, n, reverse, reverse ? 0 : flips_of(c, n), s, &done);
+        if (rc || done) return rc;
+    }
     if (reverse && reverse_on_march(c)) return run_reverse_march<R>(c, n, s);
     const bool site = c->site_mode;
     const int kc = reverse ? DIRAC_KERNEL_SPLIT : kernel_choice(c);
@@ -724,7 +761,17 @@ int dirac_step_norm(dirac_ctx *c, int64_t n, void *dev_out, void *stream) {
         if (rc) return rc;
         HIPCHK(c, hipMemcpyAsync(dev_out, res + 1, 2 * sizeof(double), hipMemcpyDeviceToDevice, s));
         return DIRAC_OK;
-    } else {
+    }
+    bool stepped = false;
+    if (tile2_applies(c)) {
+        rc = upload_tables(c, s);
+        if (rc) return rc;
+        const int64_t flips = flips_of(c, n - 1) + flips_of(c, 1);
+        rc = c->dtype == DIRAC_C64 ? run_tile2<float>(c, n, false, flips, s, &stepped)
+                                   : run_tile2<double>(c, n, false, flips, s, &stepped);
+        if (rc) return rc;
+    }
+    if (!stepped) {
         rc = dirac_step(c, n - 1, stream);
         if (rc) return rc;
     }
@@ -750,7 +797,7 @@ int dirac_step_norm(dirac_ctx *c, int64_t n, void *dev_out, void *stream) {
         if (nb <= cap) HIPCHK(c, e);   // a real launch failure
         if (c->zh) return fail(c, DIRAC_E_SHAPE, "z-slab mode: %d workgroups exceed the %d partial slots", nb, cap);
     }
-    rc = dirac_step(c, 1, stream);
+    if (!stepped) rc = dirac_step(c, 1, stream);
     if (rc) return rc;
     double *res = (double *)scratch_at(c, off_result(c));
     rc = dirac_norm_device(c, res, stream);

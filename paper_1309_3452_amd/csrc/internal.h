@@ -40,7 +40,7 @@ template <typename R> struct FusedArgs {
                           // interior planes zh .. zh + nz - 1, no wrap in z); 0 = periodic
     int px;               // two-step 3D kernel: tiles across one XCD's concurrent patch
                           // (0 = whole tile rows); set by its launcher
-    int rev;              // 3D: per-site records taken with theta -> -theta (steps of the
+    int rev;              // per-site records taken with theta -> -theta (steps of the
                           // reversed sequence; r and the table pointer are set by the caller)
 };
 
