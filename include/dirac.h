@@ -85,19 +85,21 @@ enum dirac_status {
  * steps and the conserved functional, instead of wrapping periodically.  The
  * summation by parts in the proofs of the Lemmas (Sect. 2, Sect. 3) leaves no
  * boundary terms with zero values outside either, so E_r stays exactly
- * conserved.  3D steps run on the split kernels (one launch per half-step, in
- * place); 2D ones on register tiles (below) in an even number of passes, so the
- * state stays in its buffer set, or in place where the two sets share an array.
- * Not combined with DIRAC_SLAB_Z (DIRAC_E_ARG); dirac_set_links and
+ * conserved.  Steps run in an even number of ping-pong launches, so the state
+ * stays in its buffer set, or on the split kernels (one launch per half-step, in
+ * place) for a single step, with DIRAC_KERNEL_SPLIT and where the two sets share
+ * an array.  Not combined with DIRAC_SLAB_Z (DIRAC_E_ARG); dirac_set_links and
  * dirac_adjoint_vz are refused (DIRAC_E_STATE).
  */
 #define DIRAC_ZERO_BC 4u
 
 /* step kernels (dirac_set_kernel) */
 enum dirac_kernel {
-    DIRAC_KERNEL_AUTO = 0,   /* 3D: FUSED2 where it applies, else FUSED; 2D: register
-                                tiles, up to 8 steps per launch, ping-pong, as many
-                                launches (mod 2) as FUSED2 / FUSED would make       */
+    DIRAC_KERNEL_AUTO = 0,   /* the fastest: 2D register tiles (up to 8 steps per
+                                launch), 3D the register march (up to 3) or, for
+                                complex64 V(z) tables of even nx, FUSED2; as many
+                                launches (mod 2) as FUSED2 where it applies, else
+                                FUSED, would make                                   */
     DIRAC_KERNEL_SPLIT = 1,  /* one launch per half-step, in place                 */
     DIRAC_KERNEL_FUSED = 2,  /* one launch per step, ping-pong between the buffers */
     DIRAC_KERNEL_FUSED2 = 3  /* one launch per two steps (3D: V(z) tables or
@@ -300,7 +302,7 @@ int dirac_coef_from_fields(void *coef, int dtype, double dt, double sgn_m, const
  *           kernels (default: chosen per kernel and lattice from the number of
  *           workgroups the device runs at once and each chunk's pipeline fill)
  * The two-step kernel uses 64 x 8 tiles (complex64) or 32 x 8 (complex128).
- * Every kernel gives the same bits.  In 2D a zchunk takes the march kernels.  The
+ * Every kernel gives the same bits.  With AUTO a tile_y or zchunk takes FUSED2 or FUSED.  The
  * adjoint uses its own in-place sweeps. */
 int dirac_set_kernel(dirac_ctx *ctx, int kernel, int tile_y, int zchunk);
 

@@ -13,6 +13,7 @@
 #include "ctx.h"
 #include "gauge.h"
 #include "internal.h"
+#include "march3r_plan.h"
 #include "tile2_plan.h"
 
 using namespace dirac;
@@ -268,15 +269,35 @@ int64_t flips_of(const dirac_ctx *c, int64_t n) {
     return kc == DIRAC_KERNEL_SPLIT ? 0 : kc == DIRAC_KERNEL_FUSED2 ? n / 2 + (n & 1) : n;
 }
 
+// The two buffer sets share an array: only the in-place kernels can take that.
+bool sets_shared(const dirac_ctx *c) {
+    const int narr = c->ndim == 3 ? 8 : 4;
+    for (int q = 0; q < narr; ++q)
+        for (int p = 0; p < narr; ++p)
+            if (c->buf[0][q] == c->buf[1][p]) return true;
+    return false;
+}
+
 // (2+1)D with the kernel and its knobs left to the library: several steps per
-// pass on register tiles (tile2.hip).  Not where the two buffer sets share an
-// array, which only the in-place kernels can take.
+// pass on register tiles (tile2.hip).
 bool tile2_applies(const dirac_ctx *c) {
-    if (c->ndim != 2 || c->kernel != DIRAC_KERNEL_AUTO || c->zchunk != 0 || c->links_on) return false;
-    for (int q = 0; q < 4; ++q)
-        for (int p = 0; p < 4; ++p)
-            if (c->buf[0][q] == c->buf[1][p]) return false;
-    return true;
+    return c->ndim == 2 && c->kernel == DIRAC_KERNEL_AUTO && c->zchunk == 0 && !c->links_on && !sets_shared(c);
+}
+
+// (3+1)D likewise: the register march (march3r.h) where it is the fastest kernel.
+// Per launch of two steps, next to the LDS march (one-step one for an odd
+// complex64 width, split kernels with zero values outside): complex128 256^3
+// 0.88 against 0.99 ms, with records 200 x 168 x 152 0.45 against 0.69; complex64
+// with records there 0.25 against 0.34, 191 x 151 x 127 0.13 against 0.30, zero
+// values outside 224 x 192 x 256 0.35 against 0.96.  Complex64 tables of even
+// width stay on the LDS march (256^3: 0.45 against 0.50).
+bool march3_applies(const dirac_ctx *c) {
+    if (c->ndim != 3 || c->kernel != DIRAC_KERNEL_AUTO || c->tile_y != 0 || c->zchunk != 0 || c->links_on || c->zh)
+        return false;
+    const uint64_t plane_bytes = (uint64_t)c->nx * (uint64_t)c->ny * (c->dtype == DIRAC_C64 ? 8u : 16u);
+    if (plane_bytes >= (1ull << 32)) return false;
+    if (!c->zbc && !c->site_mode && c->dtype == DIRAC_C64 && c->nx % 2 == 0) return false;
+    return !sets_shared(c);
 }
 
 // z-slab mode: the most steps one call may advance between halo refills
@@ -293,6 +314,43 @@ LinkPtrs link_ptrs(const dirac_ctx *c) {
     LinkPtrs L;
     for (int q = 0; q < 24; ++q) L.u[q] = c->links[q];
     return L;
+}
+
+// n steps as launches of three, two and one steps, in that order.
+struct March3Plan {
+    int64_t threes = 0, twos = 0, ones = 0;
+};
+
+// The split of n with the least estimated time whose launches have the parity of
+// `flips`; with sum_last its last launch has at most two steps (it also sums the
+// functional).  False if there is none (n = 1, flips even; n = 0).
+template <typename R> bool plan_march3(const dirac_ctx *c, int64_t n, int64_t flips, bool sum_last, March3Plan *out) {
+    const int most = march3r_most(sizeof(R) == 4, c->site_mode);
+    double us[4] = {};
+    for (int t = 1; t <= most; ++t)
+        us[t] = march3r_us<R>(t, c->site_mode, (int)c->nx, (int)c->ny, (int)c->nz);
+    bool found = false;
+    double best = 0.0;
+    const int64_t lo = (n + most - 1) / most, hi = n / 2 + 3 < n ? n / 2 + 3 : n;
+    for (int64_t p = lo; p <= hi; ++p) {
+        if (p < 1 || ((p ^ flips) & 1)) continue;
+        March3Plan q;
+        if (2 * p >= n) {
+            q.twos = n - p;
+            q.ones = 2 * p - n;
+        } else {
+            q.threes = n - 2 * p;
+            q.twos = 3 * p - n;
+        }
+        if (sum_last && q.twos + q.ones == 0) continue;
+        const double t = (double)q.threes * us[3] + (double)q.twos * us[2] + (double)q.ones * us[1];
+        if (!found || t < best) {
+            found = true;
+            best = t;
+            *out = q;
+        }
+    }
+    return found;
 }
 
 // The forward march kernels run the reversed sequence: with r -> -r, the
@@ -318,9 +376,35 @@ bool reverse_on_march(const dirac_ctx *c) {
     return kc == DIRAC_KERNEL_FUSED || kc == DIRAC_KERNEL_FUSED2;
 }
 
+// The launches of a plan, forward or of the reversed sequence; with npart the
+// last one sums the functional and *nblocks receives its workgroups.
+template <typename R>
+int run_march3(dirac_ctx *c, const March3Plan &plan, bool rev, hipStream_t s, double *npart, int npart_cap, int *nblocks) {
+    const int64_t p = plan.threes + plan.twos + plan.ones;
+    for (int64_t t = 0; t < p; ++t) {
+        FusedArgs<R> a = rev ? fused_args_rev<R>(c) : fused_args<R>(c);
+        if (npart && t + 1 == p) {
+            a.npart = npart;
+            a.npart_cap = npart_cap;
+        }
+        const int steps = t < plan.threes ? 3 : t < plan.threes + plan.twos ? 2 : 1;
+        HIPCHK(c, launch_march3r<R>(a, steps, c->site_mode, c->zbc, s, nblocks));
+        c->cur = 1 - c->cur;
+    }
+    return DIRAC_OK;
+}
+
 template <typename R> int run_reverse_march(dirac_ctx *c, int64_t n, hipStream_t s) {
     if (n <= 0) return DIRAC_OK;
     const bool site = c->site_mode;
+    March3Plan plan;
+    if (march3_applies(c) && (n == 1 || plan_march3<R>(c, n - 1, flips_of(c, n - 1), false, &plan))) {
+        HIPCHK(c, launch_half3<R>(half_args<R>(c, true), 1, site, s));      // H2'
+        const int rc = run_march3<R>(c, plan, true, s, nullptr, 0, nullptr);
+        if (rc) return rc;
+        HIPCHK(c, launch_half3<R>(half_args<R>(c, true), 0, site, s));      // H1'
+        return DIRAC_OK;
+    }
     HIPCHK(c, launch_half3<R>(half_args<R>(c, true), 1, site, s));      // H2'
     int64_t t = 1;
     if (kernel_choice(c) == DIRAC_KERNEL_FUSED2) {
@@ -358,7 +442,10 @@ template <typename R> int run_steps(dirac_ctx *c, int64_t n, bool reverse, hipSt
         rc = run_tile2<R>(c, n, reverse, reverse ? 0 : flips_of(c, n), s, &done);
         if (rc || done) return rc;
     }
-    if (reverse && reverse_on_march(c)) return run_reverse_march<R>(c, n, s);
+    if (reverse && (reverse_on_march(c) || (march3_applies(c) && n > 2))) return run_reverse_march<R>(c, n, s);
+    March3Plan plan;
+    if (!reverse && march3_applies(c) && plan_march3<R>(c, n, flips_of(c, n), false, &plan))
+        return run_march3<R>(c, plan, false, s, nullptr, 0, nullptr);
     const bool site = c->site_mode;
     const int kc = reverse ? DIRAC_KERNEL_SPLIT : kernel_choice(c);
     const bool fused = kc == DIRAC_KERNEL_FUSED || kc == DIRAC_KERNEL_FUSED2;
@@ -724,6 +811,22 @@ int dirac_step_norm(dirac_ctx *c, int64_t n, void *dev_out, void *stream) {
     const size_t cap_sz = partial_doubles(c) / 2;
     const int cap = cap_sz > 0x7fffffff ? 0x7fffffff : (int)cap_sz;
     const int kc = kernel_choice(c);
+    if (march3_applies(c)) {
+        rc = upload_tables(c, s);
+        if (rc) return rc;
+        March3Plan plan;
+        const int64_t flips = kc == DIRAC_KERNEL_FUSED2 && n >= 2 ? flips_of(c, n - 2) + 1 : flips_of(c, n - 1) + flips_of(c, 1);
+        const bool ok = c->dtype == DIRAC_C64 ? plan_march3<float>(c, n, flips, true, &plan)
+                                              : plan_march3<double>(c, n, flips, true, &plan);
+        if (ok) {
+            int nb = 0;
+            rc = c->dtype == DIRAC_C64 ? run_march3<float>(c, plan, false, s, part, cap, &nb)
+                                       : run_march3<double>(c, plan, false, s, part, cap, &nb);
+            if (rc) return rc;
+            HIPCHK(c, launch_final_sum(part, nb, 2, (double *)dev_out, s));
+            return DIRAC_OK;
+        }
+    }
     if (c->ndim == 3 && kc == DIRAC_KERNEL_FUSED2 && n >= 2 && !c->links_on) {
         rc = dirac_step(c, n - 2, stream);
         if (rc) return rc;

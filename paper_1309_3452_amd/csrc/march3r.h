@@ -1,0 +1,428 @@
+// (3+1)D: T time steps per launch as a z-march that lives in registers (Sect. 2,
+// Eqs. ss1-ss4).
+//
+// Along z the grid of Eq. (ABCDgrid) is a chain of half-planes: half-plane 2k
+// (z = k) holds A and D of plane k, half-plane 2k+1 (z = k + 1/2) B and C.  On
+// each, A or B is the first field of a step and D or C the second; the update of
+// the first field at half-plane g takes the second field at g-1, g, g+1 and the
+// other way round, so one kind of row serves all four equations.  With level 0
+// the old second field and level l (1 .. 2T) the fields after half-step l, the
+// march runs all levels as a pipeline, each one half-plane behind the previous:
+// iteration h loads half-plane h and evaluates level l at g = h - l from level
+// l-1 at g+1 (just computed), g and g-1, and from the old value level l-2 at g.
+// So of every level only the last three half-planes are alive, and only at the
+// thread's own cells.
+//
+// A workgroup of NW waves covers 64 x (NW K) cells of x and y: the tile plus a
+// ring of T cells on each side, recomputed (a wrong value at the rim moves one
+// cell inwards per step).  Lane l of wave w owns column l of rows w K .. w K +
+// K - 1.  x neighbours come from the next lane by a DPP wave shift, y neighbours
+// inside the thread's rows from its own registers; only the first row's component
+// 0 and the last row's component 1 of each level go through LDS.  The y neighbours
+// lie on half-plane g, computed one iteration earlier, so one barrier per
+// iteration (double-buffered edges) serves all levels.  The loop is unrolled by
+// six: windows rotate by three, the kind of half-plane and the LDS buffer by two,
+// and no value is ever moved.  The next half-plane's loads are issued at the top
+// of an iteration and land during it; the barrier waits for LDS only.
+//
+// The helpers and operation order are those of the other kernels: same bits.
+#pragma once
+
+#include <type_traits>
+
+#include "device.h"
+#include "internal.h"
+#include "march2.h"
+#include "march3r_plan.h"
+#include "ntstore.h"
+#include "stencil3.h"
+#include "tile2.h"
+
+namespace dirac {
+
+template <typename R> struct M3Rec;
+template <> struct M3Rec<float> {
+    typedef float2 T;
+    template <int SITE> static __device__ __forceinline__ Coef<float> coef(T g) {
+        return coef_site(g, SITE == 2 ? -1.0f : 1.0f);
+    }
+};
+template <> struct M3Rec<double> {
+    typedef double T;
+    template <int SITE> static __device__ __forceinline__ Coef<double> coef(T th) {
+        return coef_theta(SITE == 2 ? -th : th);
+    }
+};
+
+// z0, z1: planes of this workgroup; (tx, ty): its tile of tw x (NW K - 2T)
+// cells, tw even and at most 64 - 2T.  SITE: 0 V(z) tables, 1 per-site records, 2
+// records with theta -> -theta.  ZB: zero values outside the lattice (cells there
+// hold zero on every level).  e: 2 * 2T * 2 * NW * 64 complex values of LDS.  nrm:
+// with NORM, this thread's sums of the functional (C,D-summed form) and the plain
+// norm.  A plane is below 4 GiB.
+template <typename R, int T, int K, int NW, int SITE, bool ZB, bool NORM>
+__device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restrict__ tab, int tw, int tx, int ty,
+                                        int z0, int z1, cx<R> *e, double (&nrm)[2]) {
+    using C = cx<R>;
+    using Rec = typename M3Rec<R>::T;
+    constexpr int NL = 2 * T;
+    constexpr uint32_t CS = sizeof(C), RS = sizeof(Rec);
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nx = a.nx, ny = a.ny, nz = a.nz, zh = a.zh;
+    constexpr int th = NW * K - 2 * T;
+    const int rg = (64 - tw) / 2;
+    const int x0 = tx * tw, y0 = ty * th;
+    const int w = min(tw, nx - x0), h = min(th, ny - y0);
+    const int xl = x0 - rg + lane, yl = y0 - T + wv * K;
+    const bool inx = !ZB || (xl >= 0 && xl < nx);
+    const uint32_t pbytes = (uint32_t)nx * (uint32_t)ny * CS, rbytes = (uint32_t)nx * (uint32_t)ny * RS;
+    const uint32_t tstride = (uint32_t)(nz + 2 * zh) * (uint32_t)(4 * sizeof(R));
+    uint32_t go[K];                         // byte offset of the cell within a plane
+    bool in[K], own[K];                     // inside the lattice; in the tile
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int y = yl + k, rr = wv * K + k;
+        in[k] = inx && (!ZB || (y >= 0 && y < ny));
+        own[k] = lane >= rg && lane < rg + w && rr >= T && rr < T + h;
+        const int gy = ZB ? (in[k] ? y : 0) : wrapn(y, ny), gx = ZB ? (in[k] ? xl : 0) : wrapn(xl, nx);
+        go[k] = ((uint32_t)gy * (uint32_t)nx + (uint32_t)gx) * CS;
+    }
+    const R rx = a.rx, ry = a.ry, rz = a.rz;
+    const C zero = mk2((R)0, (R)0);
+    const int wa = min(wv + 1, NW - 1), wb = max(wv - 1, 0);
+    auto edge = [&](int buf, int l, int c, int wave) -> C & { return e[(((buf * NL + l) * 2 + c) * NW + wave) * 64 + lane]; };
+    static_assert(SITE == 0 || T <= 2, "the record windows hold three half-planes");
+    // plane of half-plane h, as it is (kr) and wrapped (kw), advanced along the march;
+    // stored index of plane kr - d: wrapped, or offset by the slab's halo (what a
+    // level computes from planes outside the halo reaches no stored value: any
+    // stored plane serves), or, with zero values outside, any plane there
+    int kr = z0 - T, kw = wrapn(kr, nz);
+    int dm[T + 2];
+#pragma unroll
+    for (int d = 0; d < T + 2; ++d) dm[d] = d % nz;
+    auto stored = [&](int d) __attribute__((always_inline)) -> int {
+        if (zh) return min(max(kr - d + zh, 0), nz + 2 * zh - 1);
+        if (d < 0) return kw + 1 == nz ? 0 : kw + 1;
+        const int k = kw - dm[d < 0 ? 0 : d];
+        return k < 0 ? k + nz : k;
+    };
+    auto inz = [&](int d) __attribute__((always_inline)) -> bool { return !ZB || (kr - d >= 0 && kr - d < nz); };
+
+    C W[NL][3][2][K];                       // [level][half-plane mod 3][component][row]
+    Rec qf[SITE ? 3 : 1][2][SITE ? K : 1], qs[SITE ? 3 : 1][2][SITE ? K : 1];    // records of the first, second field
+    C fo[2][K], sn[2][K], fn[2][K];         // old first field of h-1; next iteration's second and first
+    Rec qfn[2][SITE ? K : 1], qsn[2][SITE ? K : 1];
+#pragma unroll
+    for (int l = 0; l < NL; ++l)
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int k = 0; k < K; ++k) W[l][s][c][k] = zero;
+    if constexpr (SITE != 0)
+        for (int s = 0; s < 3; ++s)
+            for (int c = 0; c < 2; ++c)
+                for (int k = 0; k < K; ++k) {
+                    qf[s][c][k] = Rec{};
+                    qs[s][c][k] = Rec{};
+                }
+
+    const int hs = 2 * (z0 - T), he = 2 * z1 - 1 + NL;
+    // loads for iteration h: the old second field of half-plane h and the old
+    // first field of h-1 (ev: h is even); the records of the first field at h-1
+    // and of the second at h-2, where levels 1 and 2 use them.  ds, df, dq: their
+    // planes behind kr.
+    auto load = [&](auto EV, auto DS, auto DF, auto DQ) __attribute__((always_inline)) {
+        constexpr bool ev = decltype(EV)::value;
+        constexpr int ds = decltype(DS)::value, df = decltype(DF)::value, dq = decltype(DQ)::value;
+        const bool oks = inz(ds), okf = inz(df);
+        const size_t ps = (size_t)(uint32_t)stored(ds) * pbytes, pf = (size_t)(uint32_t)stored(df) * pbytes;
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const char *bs = (const char *)a.in[(ev ? 6 : 4) + c] + ps, *bf = (const char *)a.in[(ev ? 2 : 0) + c] + pf;
+                if constexpr (ZB) {
+                    sn[c][k] = zero;
+                    fn[c][k] = zero;
+                    if (oks && in[k]) sn[c][k] = *(const C *)(bs + go[k]);
+                    if (okf && in[k]) fn[c][k] = *(const C *)(bf + go[k]);
+                } else {
+                    sn[c][k] = *(const C *)(bs + go[k]);
+                    fn[c][k] = *(const C *)(bf + go[k]);
+                }
+            }
+        if constexpr (SITE != 0) {
+            const size_t qpf = (size_t)(uint32_t)stored(df) * rbytes, qps = (size_t)(uint32_t)stored(dq) * rbytes;
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    const uint32_t ro = go[k] / (CS / RS);
+                    qfn[c][k] = *(const Rec *)((const char *)a.th[(ev ? 2 : 0) + c] + qpf + ro);
+                    qsn[c][k] = *(const Rec *)((const char *)a.th[(ev ? 6 : 4) + c] + qps + ro);
+                }
+        }
+    };
+    auto tcoef = [&](int cls, int k) __attribute__((always_inline)) {
+        const R *t = (const R *)((const char *)tab + (uint32_t)cls * tstride + (uint32_t)k * (uint32_t)(4 * sizeof(R)));
+        Coef<R> q;
+        q.c1 = mk2(t[0], t[1]);
+        q.c2 = mk2(t[2], t[3]);
+        return q;
+    };
+
+    // iteration hh, hh - hs = PH (mod 6)
+    auto iter = [&](auto PH, int hh) __attribute__((always_inline)) {
+        constexpr int ph = decltype(PH)::value;
+        constexpr int bw = ph & 1, br = bw ^ 1;
+        // this iteration's inputs arrive in the windows
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                W[0][ph % 3][c][k] = sn[c][k];
+                fo[c][k] = fn[c][k];
+                if constexpr (SITE != 0) {
+                    qf[(ph + 2) % 3][c][k] = qfn[c][k];
+                    qs[(ph + 1) % 3][c][k] = qsn[c][k];
+                }
+            }
+#pragma unroll
+        for (int k = 0; k < K; ++k) asm volatile("" : "+v"(go[k]));
+        // next, for h = 2k: C and A of plane k; for h = 2k+1: D of plane k+1, B of k
+        if (hh < he)
+            load(std::integral_constant<bool, (ph & 1) == 1>(), std::integral_constant<int, (ph & 1) ? -1 : 0>(),
+                 std::integral_constant<int, 0>(), std::integral_constant<int, (ph & 1) ? 0 : 1>());
+        edge(bw, 0, 0, wv) = W[0][ph % 3][0][0];
+        edge(bw, 0, 1, wv) = W[0][ph % 3][1][K - 1];
+        auto level = [&](auto LV) __attribute__((always_inline)) {
+            constexpr int l = decltype(LV)::value;
+            constexpr bool first = l & 1;                            // the first field (A, B)
+            constexpr bool geven = ((ph + l) & 1) == 0;              // half-plane g = hh - l
+            constexpr bool rowP = first == geven;                    // A and C rows; else B and D
+            constexpr int sp = (ph + 18 - l + 1) % 3, sm = (ph + 18 - l) % 3, so = (ph + 18 - l - 1) % 3;
+            constexpr int d = (l - (ph & 1) + 1) / 2;                // plane of g: kr - d
+            const int g = hh - l;
+            const C up = edge(br, l - 1, 0, wa), dn = edge(br, l - 1, 1, wb);
+            Coef<R> kt{};
+            if constexpr (SITE == 0) kt = tcoef(first ? (geven ? 0 : 1) : (geven ? 3 : 2), stored(d));
+            const bool zin = inz(d);
+            const bool st = l >= NL - 1 && g >= 2 * z0 && g < 2 * z1;
+            const size_t po = (size_t)(uint32_t)(kr - d + zh) * pbytes;
+            C o[2][K], S[2][K];
+            // with zero values outside, the functional in complex64 takes its
+            // differences in FP64, as the reduction over the state does
+            constexpr bool wide = NORM && ZB && sizeof(R) == 4 && l == NL;
+            double2 Sd[wide ? 2 : 1][wide ? K : 1];
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const C m0 = W[l - 1][sm][0][k], m1 = W[l - 1][sm][1][k];
+                const C dz0 = csub(W[l - 1][sp][0][k], W[l - 1][so][0][k]);
+                const C dz1 = csub(W[l - 1][sp][1][k], W[l - 1][so][1][k]);
+                const C m1ym = k > 0 ? W[l - 1][sm][1][k > 0 ? k - 1 : 0] : dn;
+                const C m0yp = k + 1 < K ? W[l - 1][sm][0][k + 1 < K ? k + 1 : 0] : up;
+                if constexpr (rowP) {
+                    S[0][k] = sterm3(rz, dz0, rx, csub(m0, t2_cxm(m0)), -ry, csub(m1, m1ym));
+                    S[1][k] = sterm3(rz, dz1, rx, csub(t2_cxp(m1), m1), -ry, csub(m0yp, m0));
+                } else {
+                    S[0][k] = sterm3(-rz, dz0, rx, csub(t2_cxp(m0), m0), ry, csub(m1, m1ym));
+                    S[1][k] = sterm3(-rz, dz1, rx, csub(m1, t2_cxm(m1)), ry, csub(m0yp, m0));
+                }
+                if constexpr (wide) {
+                    auto d = [](C p, C q) { return make_double2((double)p.x - (double)q.x, (double)p.y - (double)q.y); };
+                    const C *z0p = &W[l - 1][sp][0][k], *z0m = &W[l - 1][so][0][k];
+                    const C *z1p = &W[l - 1][sp][1][k], *z1m = &W[l - 1][so][1][k];
+                    const double dx = rx, dy = rowP ? -(double)ry : (double)ry, dz = rowP ? (double)rz : -(double)rz;
+                    const C xa = rowP ? t2_cxm(m0) : t2_cxp(m0), xb = rowP ? t2_cxp(m1) : t2_cxm(m1);
+                    Sd[0][wide ? k : 0] = sterm3(dz, d(*z0p, *z0m), dx, rowP ? d(m0, xa) : d(xa, m0), dy, d(m1, m1ym));
+                    Sd[wide ? 1 : 0][wide ? k : 0] =
+                        sterm3(dz, d(*z1p, *z1m), dx, rowP ? d(xb, m1) : d(m1, xb), dy, d(m0yp, m0));
+                }
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    C old;
+                    if constexpr (l == 1) old = fo[c][k];
+                    else old = W[l >= 2 ? l - 2 : 0][sm][c][k];      // level l-2 at g: the oldest of its window
+                    Coef<R> q = kt;
+                    if constexpr (SITE != 0)
+                        q = M3Rec<R>::template coef<SITE>(first ? qf[(ph + 18 - l) % 3][c][k] : qs[(ph + 18 - l) % 3][c][k]);
+                    C v = update(old, S[c][k], q);
+                    if constexpr (ZB) v = mk2(in[k] && zin ? v.x : (R)0, in[k] && zin ? v.y : (R)0);
+                    o[c][k] = v;
+                }
+            }
+            if constexpr (l < NL) {
+                constexpr int sw = (ph + 18 - l) % 3;
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+#pragma unroll
+                    for (int k = 0; k < K; ++k) W[l < NL ? l : 0][sw][c][k] = o[c][k];
+                edge(bw, l < NL ? l : 0, 0, wv) = o[0][0];
+                edge(bw, l < NL ? l : 0, 1, wv) = o[1][K - 1];
+            }
+            if constexpr (l >= NL - 1) {
+                if (st) {
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) {
+                        constexpr int arr = first ? (geven ? 0 : 2) : (geven ? 6 : 4);
+                        char *b = (char *)a.out[arr + c] + po;
+#pragma unroll
+                        for (int k = 0; k < K; ++k)
+                            if (own[k]) {
+                                st_nt((C *)(b + go[k]), o[c][k]);
+                                if constexpr (NORM) {
+                                    const double yr = (double)o[c][k].x, yi = (double)o[c][k].y;
+                                    const double pp = yr * yr + yi * yi;
+                                    nrm[1] += pp;
+                                    double sr = (double)S[c][k].x, si = (double)S[c][k].y;
+                                    if constexpr (wide) {
+                                        sr = Sd[wide ? c : 0][wide ? k : 0].x;
+                                        si = Sd[wide ? c : 0][wide ? k : 0].y;
+                                    }
+                                    nrm[0] += first ? pp : pp + (yr * sr + yi * si);
+                                }
+                            }
+                    }
+                }
+            }
+        };
+        level(std::integral_constant<int, 1>());
+        level(std::integral_constant<int, 2>());
+        if constexpr (T > 1) {
+            level(std::integral_constant<int, (T > 1 ? 3 : 1)>());
+            level(std::integral_constant<int, (T > 1 ? 4 : 2)>());
+        }
+        if constexpr (T > 2) {
+            level(std::integral_constant<int, (T > 2 ? 5 : 1)>());
+            level(std::integral_constant<int, (T > 2 ? 6 : 2)>());
+        }
+        // the edges written, those of the previous iteration read: a barrier that
+        // waits for this wave's LDS operations only (loads and stores stay in flight)
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if constexpr (ph & 1) {
+            ++kr;
+            kw = kw + 1 == nz ? 0 : kw + 1;
+        }
+    };
+
+    // for h = hs = 2k: D of plane k, B of k-1
+    load(std::integral_constant<bool, true>(), std::integral_constant<int, 0>(), std::integral_constant<int, 1>(),
+         std::integral_constant<int, 1>());
+    for (int hh = hs; hh <= he; hh += 6) {
+        iter(std::integral_constant<int, 0>(), hh);
+        iter(std::integral_constant<int, 1>(), hh + 1);
+        if (hh + 2 > he) break;
+        iter(std::integral_constant<int, 2>(), hh + 2);
+        iter(std::integral_constant<int, 3>(), hh + 3);
+        if (hh + 4 > he) break;
+        iter(std::integral_constant<int, 4>(), hh + 4);
+        iter(std::integral_constant<int, 5>(), hh + 5);
+    }
+}
+
+template <typename R, int T, int K, int NW, int WPE, int SITE, bool ZB, bool NORM>
+__global__ __launch_bounds__(NW * 64, WPE) void k3_march3r(FusedArgs<R> a, const R *__restrict__ tab, int tw) {
+    __shared__ cx<R> e[2 * 2 * T * 2 * NW * 64];
+    __shared__ double red[NORM ? 2 * NW : 1];
+    // each XCD (blocks are dealt to the eight in turn) takes a contiguous run of tiles
+    const int n = gridDim.x, b = blockIdx.x, x = b & 7, q = n >> 3, r = n & 7;
+    const int L = x * q + min(x, r) + (b >> 3);
+    const int tx = L % a.ntx, ty = L / a.ntx % a.nty, zc = L / (a.ntx * a.nty);
+    double nrm[2] = {0.0, 0.0};
+    march3r<R, T, K, NW, SITE, ZB, NORM>(a, tab, tw, tx, ty, zc * a.zchunk, min(a.nz, (zc + 1) * a.zchunk), e, nrm);
+    if constexpr (NORM) {
+        const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) nrm[c] += __shfl_xor(nrm[c], off, 64);
+            if (lane == 0) red[2 * wv + c] = nrm[c];
+        }
+        __syncthreads();
+        if (threadIdx.x < 2) {
+            double s = 0.0;
+            for (int v = 0; v < NW; ++v) s += red[2 * v + threadIdx.x];
+            a.npart[2 * (size_t)blockIdx.x + threadIdx.x] = s;
+        }
+    }
+}
+
+// A built shape: steps per launch, rows per thread, waves, and the measured time
+// of one iteration (half-plane) of a workgroup that has a CU to itself.
+struct M3Shape {
+    int T, K, NW;
+    double iter_us;
+};
+
+// Tile width: 56 cells keep every row's stores on whole 64-byte pieces (60 of
+// them measured 13% slower at 512^3, partial lines being written twice); the full
+// 64 - 2T where that saves one of at most five tile columns.
+inline int m3_width(int nx, int T) {
+    const int full = 64 - 2 * T, nf = (nx + full - 1) / full, n56 = (nx + 55) / 56;
+    return n56 <= 5 && nf < n56 ? full : 56;
+}
+
+// Tiles, chunks and estimated microseconds of a launch.
+inline double m3_cost(const M3Shape &sh, int nx, int ny, int nz, int *tw, int *nty, int *nzc) {
+    *tw = m3_width(nx, sh.T);
+    const int th = sh.K * sh.NW - 2 * sh.T;
+    *nty = (ny + th - 1) / th;
+    const int64_t tiles = (int64_t)((nx + *tw - 1) / *tw) * *nty;
+    *nzc = pick_chunks(tiles, nz, 2 * sh.T);
+    const int64_t cus = resident_per_round(), rounds = (tiles * *nzc + cus - 1) / cus;
+    return 4.0 + (double)rounds * 2.0 * ((nz + *nzc - 1) / *nzc + 2 * sh.T) * sh.iter_us;
+}
+
+// The fastest of `count` shapes for T steps; -1 if none has T.
+inline int m3_best(const M3Shape *sh, int count, int T, int nx, int ny, int nz, double *us) {
+    int best = -1, tw, nty, nzc;
+    for (int q = 0; q < count; ++q) {
+        if (sh[q].T != T) continue;
+        const double t = m3_cost(sh[q], nx, ny, nz, &tw, &nty, &nzc);
+        if (best < 0 || t < *us) {
+            best = q;
+            *us = t;
+        }
+    }
+    return best;
+}
+
+// REC: with per-site records, else with V(z) tables.
+template <typename R, int T, int K, int NW, int WPE, bool REC>
+hipError_t m3_launch(FusedArgs<R> a, bool zb, hipStream_t s, int *nblocks_out) {
+    const M3Shape sh{T, K, NW, 1.0};
+    int tw, nzc;
+    (void)m3_cost(sh, a.nx, a.ny, a.nz, &tw, &a.nty, &nzc);
+    a.ntx = (a.nx + tw - 1) / tw;
+    a.zchunk = (a.nz + nzc - 1) / nzc;
+    a.nzc = (a.nz + a.zchunk - 1) / a.zchunk;
+    const int64_t nblk = (int64_t)a.ntx * a.nty * a.nzc;
+    if (nblk > 0x7fffffff) return hipErrorInvalidValue;
+    if (nblocks_out) *nblocks_out = (int)nblk;
+    const bool norm = a.npart != nullptr;
+    if (norm && (nblk > a.npart_cap || a.rev || T > 2)) return hipErrorInvalidValue;
+    const dim3 g((unsigned)nblk), b(NW * 64);
+#define M3(SITE, ZB, NORM) hipLaunchKernelGGL((k3_march3r<R, T, K, NW, WPE, SITE, ZB, NORM>), g, b, 0, s, a, a.tab, tw)
+    if constexpr (T > 2) {
+        if (zb) M3(0, true, false);
+        else M3(0, false, false);
+    } else if constexpr (!REC) {
+        if (norm && zb) M3(0, true, true);
+        else if (norm) M3(0, false, true);
+        else if (zb) M3(0, true, false);
+        else M3(0, false, false);
+    } else {
+        if (norm && zb) M3(1, true, true);
+        else if (norm) M3(1, false, true);
+        else if (a.rev && zb) M3(2, true, false);
+        else if (a.rev) M3(2, false, false);
+        else if (zb) M3(1, true, false);
+        else M3(1, false, false);
+    }
+#undef M3
+    return hipGetLastError();
+}
+
+}  // namespace dirac

@@ -1,0 +1,20 @@
+// Host side of the (3+1)D register march (march3r.h): the launch of 1, 2 or 3
+// steps and its estimated time.
+#pragma once
+
+#include "internal.h"
+
+namespace dirac {
+
+int resident_per_round();              // workgroups of one per CU (fused2.hip)
+// Most steps of one launch: three only with V(z) tables in complex64.
+inline int march3r_most(bool fp32, bool site) { return fp32 && !site ? 3 : 2; }
+// Estimated microseconds of a launch of `steps` steps.
+template <typename R> double march3r_us(int steps, bool site, int nx, int ny, int nz);
+// One launch of `steps` steps, in -> out, forward or (a.rev) of the reversed
+// sequence.  With a.npart (one or two steps, forward) the per-workgroup sums of
+// the functional go there.
+template <typename R>
+hipError_t launch_march3r(const FusedArgs<R> &a, int steps, bool site, bool zb, hipStream_t s, int *nblocks_out = nullptr);
+
+}  // namespace dirac
