@@ -287,16 +287,22 @@ bool tile2_applies(const dirac_ctx *c) {
 // (3+1)D likewise: the register march (march3r.h) where it is the fastest kernel.
 // Per launch of two steps, next to the LDS march (one-step one for an odd
 // complex64 width, split kernels with zero values outside): complex128 256^3
-// 0.88 against 0.99 ms, with records 200 x 168 x 152 0.45 against 0.69; complex64
-// with records there 0.25 against 0.34, 191 x 151 x 127 0.13 against 0.30, zero
-// values outside 224 x 192 x 256 0.35 against 0.96.  Complex64 tables of even
-// width stay on the LDS march (256^3: 0.45 against 0.50).
+// 0.88 against 0.99 ms, 64^3 29 against 37 us, with records 200 x 168 x 152 0.45
+// against 0.69 ms; complex64 191 x 151 x 127 0.13 against 0.30, zero values outside
+// 224 x 192 x 256 0.35 against 0.96.  For complex64 of even width the two are
+// close and the tiles' fit decides (tables: 32^3 10 against 21 us, 64^3 22 / 26,
+// 96^3 34 / 50, 128^3 88 / 79, 160^3 129 / 142, 256^3 545 / 447; records: 96^3 50 /
+// 79, 128^3 125 / 111, 200 x 168 x 152 251 / 342, 256^3 789 / 756): the estimates of
+// both, the register march's less 5%.
 bool march3_applies(const dirac_ctx *c) {
     if (c->ndim != 3 || c->kernel != DIRAC_KERNEL_AUTO || c->tile_y != 0 || c->zchunk != 0 || c->links_on || c->zh)
         return false;
     const uint64_t plane_bytes = (uint64_t)c->nx * (uint64_t)c->ny * (c->dtype == DIRAC_C64 ? 8u : 16u);
     if (plane_bytes >= (1ull << 32)) return false;
-    if (!c->zbc && !c->site_mode && c->dtype == DIRAC_C64 && c->nx % 2 == 0) return false;
+    if (!c->zbc && c->dtype == DIRAC_C64 && c->nx % 2 == 0) {
+        const int nx = (int)c->nx, ny = (int)c->ny, nz = (int)c->nz;
+        if (march3r_us<float>(2, c->site_mode, nx, ny, nz) > 0.95 * march_lds_us(c->site_mode, nx, ny, nz)) return false;
+    }
     return !sets_shared(c);
 }
 
@@ -388,7 +394,12 @@ int run_march3(dirac_ctx *c, const March3Plan &plan, bool rev, hipStream_t s, do
             a.npart_cap = npart_cap;
         }
         const int steps = t < plan.threes ? 3 : t < plan.threes + plan.twos ? 2 : 1;
-        HIPCHK(c, launch_march3r<R>(a, steps, c->site_mode, c->zbc, s, nblocks));
+        // one step: the LDS march's one-step kernel where its rows are whole (257^3
+        // complex128: 0.84 against 0.97 ms)
+        if (steps == 1 && !c->zbc && (sizeof(R) == 8 || c->nx % 2 == 0))
+            HIPCHK(c, launch_fused3<R>(a, c->site_mode, 0, s, nblocks));
+        else
+            HIPCHK(c, launch_march3r<R>(a, steps, c->site_mode, c->zbc, s, nblocks));
         c->cur = 1 - c->cur;
     }
     return DIRAC_OK;

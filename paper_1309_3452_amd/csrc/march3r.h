@@ -28,6 +28,7 @@
 // The helpers and operation order are those of the other kernels: same bits.
 #pragma once
 
+#include <algorithm>
 #include <type_traits>
 
 #include "device.h"
@@ -173,9 +174,11 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
         return q;
     };
 
-    // iteration hh, hh - hs = PH (mod 6)
-    auto iter = [&](auto PH, int hh) __attribute__((always_inline)) {
+    // iteration hh, hh - hs = PH (mod 6); FILL: hh - hs = PH, where level l has
+    // nothing yet that a stored value depends on before iteration 2 l
+    auto iter = [&](auto PH, auto FILL, int hh) __attribute__((always_inline)) {
         constexpr int ph = decltype(PH)::value;
+        constexpr int fill = decltype(FILL)::value ? ph / 2 : 2 * T;         // levels evaluated
         constexpr int bw = ph & 1, br = bw ^ 1;
         // this iteration's inputs arrive in the windows
 #pragma unroll
@@ -288,16 +291,12 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
                 }
             }
         };
-        level(std::integral_constant<int, 1>());
-        level(std::integral_constant<int, 2>());
-        if constexpr (T > 1) {
-            level(std::integral_constant<int, (T > 1 ? 3 : 1)>());
-            level(std::integral_constant<int, (T > 1 ? 4 : 2)>());
-        }
-        if constexpr (T > 2) {
-            level(std::integral_constant<int, (T > 2 ? 5 : 1)>());
-            level(std::integral_constant<int, (T > 2 ? 6 : 2)>());
-        }
+        if constexpr (fill >= 1) level(std::integral_constant<int, 1>());
+        if constexpr (fill >= 2) level(std::integral_constant<int, 2>());
+        if constexpr (T > 1 && fill >= 3) level(std::integral_constant<int, (T > 1 ? 3 : 1)>());
+        if constexpr (T > 1 && fill >= 4) level(std::integral_constant<int, (T > 1 ? 4 : 2)>());
+        if constexpr (T > 2 && fill >= 5) level(std::integral_constant<int, (T > 2 ? 5 : 1)>());
+        if constexpr (T > 2 && fill >= 6) level(std::integral_constant<int, (T > 2 ? 6 : 2)>());
         // the edges written, those of the previous iteration read: a barrier that
         // waits for this wave's LDS operations only (loads and stores stay in flight)
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -310,15 +309,24 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
     // for h = hs = 2k: D of plane k, B of k-1
     load(std::integral_constant<bool, true>(), std::integral_constant<int, 0>(), std::integral_constant<int, 1>(),
          std::integral_constant<int, 1>());
-    for (int hh = hs; hh <= he; hh += 6) {
-        iter(std::integral_constant<int, 0>(), hh);
-        iter(std::integral_constant<int, 1>(), hh + 1);
+    // 2 (z1 - z0) + 4 T iterations: an even number, at least six
+    constexpr std::true_type filling{};
+    constexpr std::false_type full{};
+    iter(std::integral_constant<int, 0>(), filling, hs);
+    iter(std::integral_constant<int, 1>(), filling, hs + 1);
+    iter(std::integral_constant<int, 2>(), filling, hs + 2);
+    iter(std::integral_constant<int, 3>(), filling, hs + 3);
+    iter(std::integral_constant<int, 4>(), filling, hs + 4);
+    iter(std::integral_constant<int, 5>(), filling, hs + 5);
+    for (int hh = hs + 6; hh <= he; hh += 6) {
+        iter(std::integral_constant<int, 0>(), full, hh);
+        iter(std::integral_constant<int, 1>(), full, hh + 1);
         if (hh + 2 > he) break;
-        iter(std::integral_constant<int, 2>(), hh + 2);
-        iter(std::integral_constant<int, 3>(), hh + 3);
+        iter(std::integral_constant<int, 2>(), full, hh + 2);
+        iter(std::integral_constant<int, 3>(), full, hh + 3);
         if (hh + 4 > he) break;
-        iter(std::integral_constant<int, 4>(), hh + 4);
-        iter(std::integral_constant<int, 5>(), hh + 5);
+        iter(std::integral_constant<int, 4>(), full, hh + 4);
+        iter(std::integral_constant<int, 5>(), full, hh + 5);
     }
 }
 
@@ -349,11 +357,19 @@ __global__ __launch_bounds__(NW * 64, WPE) void k3_march3r(FusedArgs<R> a, const
     }
 }
 
-// A built shape: steps per launch, rows per thread, waves, and the measured time
-// of one iteration (half-plane) of a workgroup that has a CU to itself.
+// A built shape: steps per launch, rows per thread, waves, workgroups a CU holds at
+// once (by LDS), and the measured time of one iteration (half-plane) of a workgroup
+// that has a CU to itself; two on a CU take 1.45 times that each.
 struct M3Shape {
-    int T, K, NW;
+    int T, K, NW, occ;
     double iter_us;
+};
+
+// How a launch of T steps runs: shape (-1: none has T), tile width, tiles in y,
+// chunks in z, and its estimated time.
+struct M3Pick {
+    int shape = -1, tw = 0, nty = 0, nzc = 0;
+    double us = 0.0;
 };
 
 // Tile width: 56 cells keep every row's stores on whole 64-byte pieces (60 of
@@ -364,39 +380,53 @@ inline int m3_width(int nx, int T) {
     return n56 <= 5 && nf < n56 ? full : 56;
 }
 
-// Tiles, chunks and estimated microseconds of a launch.
-inline double m3_cost(const M3Shape &sh, int nx, int ny, int nz, int *tw, int *nty, int *nzc) {
-    *tw = m3_width(nx, sh.T);
-    const int th = sh.K * sh.NW - 2 * sh.T;
-    *nty = (ny + th - 1) / th;
-    const int64_t tiles = (int64_t)((nx + *tw - 1) / *tw) * *nty;
-    *nzc = pick_chunks(tiles, nz, 2 * sh.T);
-    const int64_t cus = resident_per_round(), rounds = (tiles * *nzc + cus - 1) / cus;
-    return 4.0 + (double)rounds * 2.0 * ((nz + *nzc - 1) / *nzc + 2 * sh.T) * sh.iter_us;
-}
-
-// The fastest of `count` shapes for T steps; -1 if none has T.
-inline int m3_best(const M3Shape *sh, int count, int T, int nx, int ny, int nz, double *us) {
-    int best = -1, tw, nty, nzc;
+// The fastest of `count` shapes for T steps.  A chunk of p planes takes 2 p + 4 T
+// iterations, of which the filling ones evaluate few levels: together they cost
+// about 2 (p + T).  Workgroups run in rounds of one or two per CU.  The last pick
+// for each (T, records) is kept per thread.
+inline const M3Pick &m3_pick(const M3Shape *sh, int count, int T, bool rec, int nx, int ny, int nz) {
+    struct Memo {
+        int nx = -1, ny = -1, nz = -1;
+        const M3Shape *sh = nullptr;
+        M3Pick pick;
+    };
+    static thread_local Memo memo[4][2];
+    Memo &m = memo[T & 3][rec ? 1 : 0];
+    if (m.sh == sh && m.nx == nx && m.ny == ny && m.nz == nz) return m.pick;
+    M3Pick best;
+    const int64_t cus = resident_per_round();
     for (int q = 0; q < count; ++q) {
         if (sh[q].T != T) continue;
-        const double t = m3_cost(sh[q], nx, ny, nz, &tw, &nty, &nzc);
-        if (best < 0 || t < *us) {
-            best = q;
-            *us = t;
+        M3Pick p;
+        p.shape = q;
+        p.tw = m3_width(nx, T);
+        p.nty = (ny + sh[q].K * sh[q].NW - 2 * T - 1) / (sh[q].K * sh[q].NW - 2 * T);
+        const int64_t tiles = (int64_t)((nx + p.tw - 1) / p.tw) * p.nty;
+        for (int occ = 1; occ <= sh[q].occ; ++occ) {
+            const int64_t per = cus * occ, cap = std::min<int64_t>(nz, 8 * ((per + tiles - 1) / tiles));
+            for (int64_t c = 1; c <= cap; ++c) {
+                p.nzc = (int)c;
+                p.us = 4.0 + (double)((tiles * c + per - 1) / per) * 2.0 * (double)((nz + c - 1) / c + T) *
+                                 sh[q].iter_us * (occ == 1 ? 1.0 : 1.45);
+                if (best.shape < 0 || p.us < best.us) best = p;
+            }
         }
     }
-    return best;
+    m.sh = sh;
+    m.nx = nx;
+    m.ny = ny;
+    m.nz = nz;
+    m.pick = best;
+    return m.pick;
 }
 
 // REC: with per-site records, else with V(z) tables.
 template <typename R, int T, int K, int NW, int WPE, bool REC>
-hipError_t m3_launch(FusedArgs<R> a, bool zb, hipStream_t s, int *nblocks_out) {
-    const M3Shape sh{T, K, NW, 1.0};
-    int tw, nzc;
-    (void)m3_cost(sh, a.nx, a.ny, a.nz, &tw, &a.nty, &nzc);
+hipError_t m3_launch(FusedArgs<R> a, const M3Pick &pick, bool zb, hipStream_t s, int *nblocks_out) {
+    const int tw = pick.tw;
     a.ntx = (a.nx + tw - 1) / tw;
-    a.zchunk = (a.nz + nzc - 1) / nzc;
+    a.nty = pick.nty;
+    a.zchunk = (a.nz + pick.nzc - 1) / pick.nzc;
     a.nzc = (a.nz + a.zchunk - 1) / a.zchunk;
     const int64_t nblk = (int64_t)a.ntx * a.nty * a.nzc;
     if (nblk > 0x7fffffff) return hipErrorInvalidValue;

@@ -6,30 +6,32 @@ namespace dirac {
 namespace {
 // Tables: 16 rows by 8 waves of up to 256 registers (LDS edges take 128 KB), or 8
 // rows; records: 8 rows.
-constexpr M3Shape kTab[] = {{1, 2, 8, 4.8}, {2, 2, 8, 3.5}, {2, 1, 8, 1.4}};
-constexpr M3Shape kSite[] = {{1, 2, 8, 5.6}, {2, 1, 8, 2.15}};
+constexpr M3Shape kTab[] = {{1, 2, 8, 1, 4.8}, {2, 2, 8, 1, 3.5}, {2, 1, 8, 1, 1.4}};
+constexpr M3Shape kSite[] = {{1, 2, 8, 1, 5.6}, {2, 1, 8, 1, 2.15}};
 constexpr int kNTab = sizeof(kTab) / sizeof(kTab[0]), kNSite = sizeof(kSite) / sizeof(kSite[0]);
+
+const M3Pick &pick(int steps, bool site, int nx, int ny, int nz) {
+    return m3_pick(site ? kSite : kTab, site ? kNSite : kNTab, steps, site, nx, ny, nz);
+}
 }  // namespace
 
 template <> double march3r_us<double>(int steps, bool site, int nx, int ny, int nz) {
-    double us = 0.0;
-    m3_best(site ? kSite : kTab, site ? kNSite : kNTab, steps, nx, ny, nz, &us);
-    return us;
+    return pick(steps, site, nx, ny, nz).us;
 }
 
 template <>
 hipError_t launch_march3r<double>(const FusedArgs<double> &a, int steps, bool site, bool zb, hipStream_t s,
                                   int *nblocks_out) {
-    double us = 0.0;
-    const int q = m3_best(site ? kSite : kTab, site ? kNSite : kNTab, steps, a.nx, a.ny, a.nz, &us);
+    const M3Pick &p = pick(steps, site, a.nx, a.ny, a.nz);
+    const int q = p.shape;
     if (site) {
-        if (q == 0) return m3_launch<double, 1, 2, 8, 2, true>(a, zb, s, nblocks_out);
-        if (q == 1) return m3_launch<double, 2, 1, 8, 2, true>(a, zb, s, nblocks_out);
+        if (q == 0) return m3_launch<double, 1, 2, 8, 2, true>(a, p, zb, s, nblocks_out);
+        if (q == 1) return m3_launch<double, 2, 1, 8, 2, true>(a, p, zb, s, nblocks_out);
         return hipErrorInvalidValue;
     }
-    if (q == 0) return m3_launch<double, 1, 2, 8, 2, false>(a, zb, s, nblocks_out);
-    if (q == 1) return m3_launch<double, 2, 2, 8, 2, false>(a, zb, s, nblocks_out);
-    if (q == 2) return m3_launch<double, 2, 1, 8, 2, false>(a, zb, s, nblocks_out);
+    if (q == 0) return m3_launch<double, 1, 2, 8, 2, false>(a, p, zb, s, nblocks_out);
+    if (q == 1) return m3_launch<double, 2, 2, 8, 2, false>(a, p, zb, s, nblocks_out);
+    if (q == 2) return m3_launch<double, 2, 1, 8, 2, false>(a, p, zb, s, nblocks_out);
     return hipErrorInvalidValue;
 }
 

@@ -11,6 +11,14 @@ int resident_per_round();              // workgroups of one per CU (fused2.hip)
 inline int march3r_most(bool fp32, bool site) { return fp32 && !site ? 3 : 2; }
 // Estimated microseconds of a launch of `steps` steps.
 template <typename R> double march3r_us(int steps, bool site, int nx, int ny, int nz);
+// The same for two steps of the LDS march on complex64 lattices of even width
+// (fused2.hip): its workgroups spend about 3.3 us on a plane, 5.4 with records.
+inline double march_lds_us(bool site, int nx, int ny, int nz) {
+    const int64_t tiles = (int64_t)((nx + 63) / 64) * ((ny + 7) / 8), cus = resident_per_round();
+    const int nzc = pick_chunks(tiles, nz, 6);
+    return 2.0 + (double)((tiles * nzc + cus - 1) / cus) * ((nz + nzc - 1) / nzc + 6) *
+                     (site ? 5.4 : 3.3);
+}
 // One launch of `steps` steps, in -> out, forward or (a.rev) of the reversed
 // sequence.  With a.npart (one or two steps, forward) the per-workgroup sums of
 // the functional go there.
