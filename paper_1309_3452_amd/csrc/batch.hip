@@ -41,6 +41,7 @@
 #include "internal.h"
 #include "march2.h"
 #include "march2x2.h"
+#include "norm2.h"
 #include "tile2.h"
 #include "tile2_plan.h"
 
@@ -862,30 +863,30 @@ int dirac_batch_norms(dirac_ctx *c, double *out, void *stream) {
     const BLayout Ly = blayout(c);
     double *part = (double *)((char *)c->scratch + Ly.partial);
     double *res = (double *)((char *)c->scratch + Ly.result);
-    for (int64_t b = 0; b < c->count; ++b) {
-        const std::vector<void *> &buf = c->cur == 0 ? c->bstate : c->bpartner;
-        if (c->dtype == DIRAC_C64) {
-            ReduceArgs<float> a;
-            memset(&a, 0, sizeof a);
-            for (int q = 0; q < 4; ++q) a.f[q] = buf[(size_t)b * 4 + q];
-            a.rx = a.ry = (float)c->bdt[(size_t)b];
-            a.nx = (int)c->bnx[(size_t)b];
-            a.ny = (int)c->bny[(size_t)b];
-            a.nz = 1;
-            a.partial = part;
-            BCHK(c, launch_norm2<float>(a, s));
-        } else {
-            ReduceArgs<double> a;
-            memset(&a, 0, sizeof a);
-            for (int q = 0; q < 4; ++q) a.f[q] = buf[(size_t)b * 4 + q];
-            a.rx = a.ry = c->bdt[(size_t)b];
-            a.nx = (int)c->bnx[(size_t)b];
-            a.ny = (int)c->bny[(size_t)b];
-            a.nz = 1;
-            a.partial = part;
-            BCHK(c, launch_norm2<double>(a, s));
+    const std::vector<void *> &buf = c->cur == 0 ? c->bstate : c->bpartner;
+    for (int64_t b0 = 0; b0 < c->count; b0 += kNormGroup) {
+        Norm2Group g;
+        memset(&g, 0, sizeof g);
+        g.count = (int)std::min<int64_t>(kNormGroup, c->count - b0);
+        g.partial = part;
+        double cells = 0.0;
+        for (int b = 0; b < g.count; ++b) cells += (double)c->bnx[(size_t)(b0 + b)] * (double)c->bny[(size_t)(b0 + b)];
+        // the partial slots, shared out by cells (at least one each)
+        for (int b = 0; b < g.count; ++b) {
+            const size_t l = (size_t)(b0 + b);
+            Norm2Lat &L = g.lat[b];
+            for (int q = 0; q < 4; ++q) L.f[q] = buf[l * 4 + q];
+            L.nx = (int)c->bnx[l];
+            L.ny = (int)c->bny[l];
+            L.r = c->dtype == DIRAC_C64 ? (double)(float)c->bdt[l] : c->bdt[l];
+            const double n = (double)L.nx * L.ny;
+            int blocks = 1 + (int)((kReduceBlocks - kNormGroup) * (n / cells));
+            const int64_t need = ((int64_t)L.nx * L.ny + kReduceThreads - 1) / kReduceThreads;
+            if (blocks > need) blocks = (int)need;
+            g.first[b + 1] = g.first[b] + blocks;
         }
-        BCHK(c, launch_final_sum(part, kReduceBlocks, kNormVals, res + (size_t)b * kNormVals, s));
+        BCHK(c, c->dtype == DIRAC_C64 ? launch_norm2_group<float>(g, res + (size_t)b0 * kNormVals, s)
+                                      : launch_norm2_group<double>(g, res + (size_t)b0 * kNormVals, s));
     }
     BCHK(c, hipMemcpyAsync(out, res, (size_t)c->count * kNormVals * sizeof(double), hipMemcpyDeviceToHost, s));
     BCHK(c, hipStreamSynchronize(s));

@@ -8,7 +8,7 @@ namespace {
 // rows where those fill the chip better; three steps per launch with 24 or 12
 // rows.  Records add 24 registers per cell: 16 rows by 8 waves, or 8.
 constexpr M3Shape kTab[] = {{1, 4, 8, 1, 5.0}, {2, 2, 16, 1, 4.6}, {2, 1, 16, 1, 2.0}, {2, 1, 8, 2, 1.07},
-                             {3, 3, 8, 1, 4.8}, {3, 1, 12, 1, 2.05}};
+                             {3, 3, 8, 1, 5.8}, {3, 1, 12, 1, 2.05}};
 constexpr M3Shape kSite[] = {{1, 2, 8, 1, 3.6}, {2, 2, 8, 1, 3.3}, {2, 1, 8, 1, 1.25}};
 constexpr int kNTab = sizeof(kTab) / sizeof(kTab[0]), kNSite = sizeof(kSite) / sizeof(kSite[0]);
 

@@ -1,5 +1,7 @@
 // Single-lattice launches of the (2+1)D register tile (tile2.h) and the rule that
 // splits a number of steps into passes, shared with the batches.
+#include <math.h>
+
 #include <algorithm>
 
 #include "tile2.h"
@@ -45,22 +47,22 @@ int64_t tile2_tiles(int shape, int ring, int64_t nx, int64_t ny) {
 // Microseconds of one pass of `steps` steps over `tiles` tiles holding `cells`
 // lattice cells: a launch costs 3.2; a CU evaluates a region cell in 0.66 ns
 // (complex64), 0.85 ns (complex128) or 1.4 ns (complex128 per site, one workgroup
-// per CU), counting whole rounds while there are few; the passes of a lattice
-// whose two sets and records leave the caches move their bytes at 5 TB/s.  These
-// figures reproduce the measured times above within 15% and, over the lattices of
-// a sweep from 7 x 5 to 4096 x 4096 in both types, pick the best steps per pass
-// and shape or one within 5% of it.
+// per CU), counting whole rounds while there are few, 1.6 times that where eight
+// waves have a CU to themselves; the bytes of one pass go at 5 TB/s, 9 out of the
+// caches.  Both overlap, the longer one only in part (cube root of the sum of
+// cubes: 2047 x 1531 complex64 per site measured 77, 84, 105 us for 5, 6, 7 steps
+// with 62, 82, 105 us of arithmetic and 60 of bytes).
 double tile2_pass_us(int shape, int steps, int64_t tiles, double cells, bool fp32, bool site) {
     const double cus = resident_per_round();
     double per = (double)tiles / cus;
     if (per <= 4.0) per = (double)((tiles + (int64_t)cus - 1) / (int64_t)cus);
     double rows = (double)tile2_rows(shape) * steps;
     if (shape == 0) rows -= (double)steps * (steps - 1);          // the waves that skip
-    const double cell_ns = fp32 ? 0.66 : site ? 1.4 : 0.85;
+    const double cell_ns = (fp32 ? 0.66 : site ? 1.4 : 0.85) * (shape == 2 && per < 2.0 ? 1.6 : 1.0);
     const double comp = per * rows * 64.0 * cell_ns * 1e-3;
     const double bytes = cells * ((fp32 ? 64.0 : 128.0) + (site ? 32.0 : 0.0));
     const double mem = bytes / (bytes > 2e8 ? 5e6 : 9e6);
-    return 3.2 + std::max(comp, mem);
+    return 3.2 + cbrt(comp * comp * comp + mem * mem * mem);
 }
 
 int tile2_best_shape(int steps, int64_t count, const int64_t *nx, const int64_t *ny, bool fp32, bool site, double *us) {
