@@ -33,7 +33,6 @@ struct dirac_ctx {
     std::vector<double> w_int, w_half;    // Im V(z) (absorbing layers), empty if none
     bool tab_dirty = true;
     std::vector<double> tab_host64;
-    std::vector<float> tab_host32;
     void *theta[8] = {};
     bool site_mode = false;
 

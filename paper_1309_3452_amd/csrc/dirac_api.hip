@@ -9,7 +9,7 @@
 #include <vector>
 
 #include "../../include/dirac.h"
-#include "cayley32.h"
+#include "cayley.h"
 #include "ctx.h"
 #include "gauge.h"
 #include "internal.h"
@@ -47,59 +47,6 @@ int fail(dirac_ctx *c, int code, const char *fmt, ...) {
 bool finite_pos(double v) { return isfinite(v) && v > 0.0; }
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
-
-// FP64 Cayley coefficients, every operation rounded on its own.
-void cayley64(double th, double out[4]) {
-#pragma clang fp contract(off)
-    double t2 = th * th;
-    double d = 1.0 + t2;
-    out[0] = (1.0 - t2) / d;
-    out[1] = -((2.0 * th) / d);
-    out[2] = 1.0 / d;
-    out[3] = -(th / d);
-}
-
-// FP32 increment-form coefficients: gamma = 2 i th / (1 + i th) by the
-// unit-modulus rounding shared with the device records (cayley32.h), beta =
-// 1 / (1 + i th) rounded from FP64.
-void cayley32(double th, float out[4]) {
-#pragma clang fp contract(off)
-    const double d = 1.0 + th * th;
-    gamma32_search(th, &out[0], &out[1]);
-    out[2] = (float)(1.0 / d);
-    out[3] = (float)(-th / d);
-}
-
-// Complex theta = th + i thi (a complex potential; Im V damps for Im V < 0):
-// with 1 + i theta = (1 - thi) + i th and 1 - i theta = (1 + thi) - i th,
-//   beta = ((1 - thi) - i th)/den,  alpha = ((1 - thi^2 - th^2) - 2 i th)/den,
-//   den = (1 - thi)^2 + th^2.
-void cayley64c(double th, double thi, double out[4]) {
-#pragma clang fp contract(off)
-    if (thi == 0.0) {
-        cayley64(th, out);
-        return;
-    }
-    const double den = (1.0 - thi) * (1.0 - thi) + th * th;
-    out[0] = (1.0 - thi * thi - th * th) / den;
-    out[1] = -((2.0 * th) / den);
-    out[2] = (1.0 - thi) / den;
-    out[3] = -(th / den);
-}
-// FP32 increment form for a complex theta: gamma = 1 - alpha and beta rounded
-// from FP64 (|alpha| != 1, so the unit-modulus search does not apply).
-void cayley32c(double th, double thi, float out[4]) {
-    if (thi == 0.0) {
-        cayley32(th, out);
-        return;
-    }
-    double c[4];
-    cayley64c(th, thi, c);
-    out[0] = (float)(1.0 - c[0]);
-    out[1] = (float)(-c[1]);
-    out[2] = (float)c[2];
-    out[3] = (float)c[3];
-}
 
 // Planes of the V(z) tables and per-site fields: the interior plus, in z-slab
 // mode, the halo planes on both sides.
@@ -171,18 +118,24 @@ int upload_tables(dirac_ctx *c, hipStream_t s) {
         HIPCHK(c, hipMemcpyAsync(scratch_at(c, off_tab(c) + align256(half)), c->tab_host64.data() + 4 * nz * 4,
                                  half, hipMemcpyHostToDevice, s));
     } else {
-        c->tab_host32.assign((size_t)2 * 4 * nz * 4, 0.0f);
+        // theta goes up in the entries' place and becomes the entry there: the
+        // unit-modulus search took the host 1 us an entry (256 planes: 2.2 ms of a
+        // first step)
+        c->tab_host64.assign((size_t)2 * 4 * nz * 2, 0.0);
         for (int dir = 0; dir < 2; ++dir)
             for (int q = 0; q < 4; ++q)
                 for (int64_t k = 0; k < nz; ++k) {
-                    double th = theta_of(c, q, k), thi = theta_im_of(c, q, k);
-                    cayley32c(dir == 0 ? th : -th, dir == 0 ? thi : -thi,
-                              &c->tab_host32[(((size_t)dir * 4 + q) * nz + k) * 4]);
+                    const double th = theta_of(c, q, k), thi = theta_im_of(c, q, k);
+                    double *e = &c->tab_host64[(((size_t)dir * 4 + q) * nz + k) * 2];
+                    e[0] = dir == 0 ? th : -th;
+                    e[1] = dir == 0 ? thi : -thi;
                 }
-        size_t half = tab_bytes<float>(c);
-        HIPCHK(c, hipMemcpyAsync(scratch_at(c, off_tab(c)), c->tab_host32.data(), half, hipMemcpyHostToDevice, s));
-        HIPCHK(c, hipMemcpyAsync(scratch_at(c, off_tab(c) + align256(half)), c->tab_host32.data() + 4 * nz * 4,
-                                 half, hipMemcpyHostToDevice, s));
+        const size_t half = tab_bytes<float>(c);
+        for (int dir = 0; dir < 2; ++dir) {
+            void *t = scratch_at(c, off_tab(c) + dir * align256(half));
+            HIPCHK(c, hipMemcpyAsync(t, c->tab_host64.data() + (size_t)dir * 4 * nz * 2, half, hipMemcpyHostToDevice, s));
+            HIPCHK(c, launch_table32(t, 4 * nz, s));
+        }
     }
     // the host staging vectors stay alive in the context until the next upload
     HIPCHK(c, hipStreamSynchronize(s));

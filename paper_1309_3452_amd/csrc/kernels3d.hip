@@ -13,6 +13,7 @@
 //   S_C1 =  rz(A1[k+1] - A1) + rx(B1[i+1] - B1) - i ry(B0[j+1] - B0)
 //   S_D0 = -rz(B0 - B0[k-1]) + rx(A0[i+1] - A0) + i ry(A1 - A1[j-1])
 //   S_D1 = -rz(B1 - B1[k-1]) + rx(A1 - A1[i-1]) + i ry(A0[j+1] - A0)
+#include "cayley.h"
 #include "device.h"
 #include "internal.h"
 #include "norm3.h"
@@ -379,6 +380,16 @@ __global__ __launch_bounds__(256) void k_coef_from_theta(float2 *coef, const dou
         coef[t] = gamma32_complex(theta[t], theta_im ? theta_im[t] : 0.0);
 }
 
+// Table entries in place: four floats where the two doubles of theta were.
+__global__ __launch_bounds__(64) void k_table32(double2 *tab, int64_t n) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= n) return;
+    const double2 th = tab[t];
+    float e[4];
+    cayley32c(th.x, th.y, e);
+    ((float4 *)tab)[t] = make_float4(e[0], e[1], e[2], e[3]);
+}
+
 // Per-site record from the fields of one state array: theta = half_dt (sgn_m +
 // V) + i half_dt W in FP64, then gamma (complex64 lattices) or theta itself.
 template <bool C64>
@@ -481,6 +492,12 @@ hipError_t launch_coef_from_theta(void *coef, const double *theta, const double 
                                   hipStream_t s) {
     hipLaunchKernelGGL(k_coef_from_theta, dim3(grid_for(n, 256, 8192)), dim3(256), 0, s, (float2 *)coef, theta,
                        theta_im, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_table32(void *tab, int64_t n, hipStream_t s) {
+    if (n < 1 || (n + 63) / 64 > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_table32, dim3((unsigned)((n + 63) / 64)), dim3(64), 0, s, (double2 *)tab, n);
     return hipGetLastError();
 }
 
