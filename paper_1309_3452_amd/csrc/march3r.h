@@ -51,14 +51,23 @@ template <> struct M3Rec<float> {
 template <> struct M3Rec<double> {
     typedef double T;
     template <int SITE> static __device__ __forceinline__ Coef<double> coef(T th) {
-        return coef_theta(SITE == 2 ? -th : th);
+        return coef_theta_r(SITE == 2 ? -th : th);
     }
 };
+
+// Twelve waves of complex128 rows would need 192 KB for double-buffered edges.  They
+// take single ones and a second barrier, between levels 2 and 3: edges of levels 0
+// and 1 are read before it and written after it, those of levels 2 and 3 read
+// after it and written before it, in the next iteration.
+template <typename R, int T, int K, int NW> constexpr bool m3_single() { return sizeof(R) == 8 && T == 2 && NW > 8; }
+template <typename R, int T, int K, int NW> constexpr int m3_edges() {
+    return (m3_single<R, T, K, NW>() ? 1 : 2) * 2 * T * 2 * NW * 64;
+}
 
 // z0, z1: planes of this workgroup; (tx, ty): its tile of tw x (NW K - 2T)
 // cells, tw even and at most 64 - 2T.  SITE: 0 V(z) tables, 1 per-site records, 2
 // records with theta -> -theta.  ZB: zero values outside the lattice (cells there
-// hold zero on every level).  e: 2 * 2T * 2 * NW * 64 complex values of LDS.  nrm:
+// hold zero on every level).  e: m3_edges complex values of LDS.  nrm:
 // with NORM, this thread's sums of the functional (C,D-summed form) and the plain
 // norm.  A plane is below 4 GiB.
 template <typename R, int T, int K, int NW, int SITE, bool ZB, bool NORM>
@@ -91,8 +100,10 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
     const R rx = a.rx, ry = a.ry, rz = a.rz;
     const C zero = mk2((R)0, (R)0);
     const int wa = min(wv + 1, NW - 1), wb = max(wv - 1, 0);
-    auto edge = [&](int buf, int l, int c, int wave) -> C & { return e[(((buf * NL + l) * 2 + c) * NW + wave) * 64 + lane]; };
-    static_assert(SITE == 0 || T <= 2, "the record windows hold three half-planes");
+    constexpr bool SB = m3_single<R, T, K, NW>();
+    auto edge = [&](int buf, int l, int c, int wave) -> C & {
+        return e[((((SB ? 0 : buf) * NL + l) * 2 + c) * NW + wave) * 64 + lane];
+    };
     // plane of half-plane h, as it is (kr) and wrapped (kw), advanced along the march;
     // stored index of plane kr - d: wrapped, or offset by the slab's halo (what a
     // level computes from planes outside the halo reaches no stored value: any
@@ -110,7 +121,10 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
     auto inz = [&](int d) __attribute__((always_inline)) -> bool { return !ZB || (kr - d >= 0 && kr - d < nz); };
 
     C W[NL][3][2][K];                       // [level][half-plane mod 3][component][row]
-    Rec qf[SITE ? 3 : 1][2][SITE ? K : 1], qs[SITE ? 3 : 1][2][SITE ? K : 1];    // records of the first, second field
+    static_assert(SITE == 0 || T <= 2, "the record windows hold three half-planes");
+    // records of the first, second field [half-plane mod 3]: each serves two levels
+    // (loaded a second time for levels 3 and 4 they cost a third more time)
+    Rec qf[SITE ? 3 : 1][2][SITE ? K : 1], qs[SITE ? 3 : 1][2][SITE ? K : 1];
     C fo[2][K], sn[2][K], fn[2][K];         // old first field of h-1; next iteration's second and first
     Rec qfn[2][SITE ? K : 1], qsn[2][SITE ? K : 1];
 #pragma unroll
@@ -120,8 +134,7 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
 #pragma unroll
             for (int c = 0; c < 2; ++c)
 #pragma unroll
-                for (int k = 0; k < K; ++k) W[l][s][c][k] = zero;
-    if constexpr (SITE != 0)
+                for (int k = 0; k < K; ++k) W[l][s][c][k] = zero;    if constexpr (SITE != 0)
         for (int s = 0; s < 3; ++s)
             for (int c = 0; c < 2; ++c)
                 for (int k = 0; k < K; ++k) {
@@ -198,8 +211,18 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
         if (hh < he)
             load(std::integral_constant<bool, (ph & 1) == 1>(), std::integral_constant<int, (ph & 1) ? -1 : 0>(),
                  std::integral_constant<int, 0>(), std::integral_constant<int, (ph & 1) ? 0 : 1>());
-        edge(bw, 0, 0, wv) = W[0][ph % 3][0][0];
-        edge(bw, 0, 1, wv) = W[0][ph % 3][1][K - 1];
+        // edges of level l's newest half-plane, of this iteration or (ago = 1) the last
+        auto put = [&](auto LV, int ago) __attribute__((always_inline)) {
+            constexpr int l = decltype(LV)::value;
+            edge(bw, l, 0, wv) = W[l][(ph + 18 - l - ago) % 3][0][0];
+            edge(bw, l, 1, wv) = W[l][(ph + 18 - l - ago) % 3][1][K - 1];
+        };
+        if constexpr (SB) {
+            put(std::integral_constant<int, 2>(), 1);
+            put(std::integral_constant<int, 3>(), 1);
+        } else {
+            put(std::integral_constant<int, 0>(), 0);
+        }
         auto level = [&](auto LV) __attribute__((always_inline)) {
             constexpr int l = decltype(LV)::value;
             constexpr bool first = l & 1;                            // the first field (A, B)
@@ -262,8 +285,7 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
                 for (int c = 0; c < 2; ++c)
 #pragma unroll
                     for (int k = 0; k < K; ++k) W[l < NL ? l : 0][sw][c][k] = o[c][k];
-                edge(bw, l < NL ? l : 0, 0, wv) = o[0][0];
-                edge(bw, l < NL ? l : 0, 1, wv) = o[1][K - 1];
+                if constexpr (!SB) put(std::integral_constant<int, (l < NL ? l : 0)>(), 0);
             }
             if constexpr (l >= NL - 1) {
                 if (st) {
@@ -293,6 +315,11 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
         };
         if constexpr (fill >= 1) level(std::integral_constant<int, 1>());
         if constexpr (fill >= 2) level(std::integral_constant<int, 2>());
+        if constexpr (SB) {
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            put(std::integral_constant<int, 0>(), 0);
+            put(std::integral_constant<int, 1>(), 0);
+        }
         if constexpr (T > 1 && fill >= 3) level(std::integral_constant<int, (T > 1 ? 3 : 1)>());
         if constexpr (T > 1 && fill >= 4) level(std::integral_constant<int, (T > 1 ? 4 : 2)>());
         if constexpr (T > 2 && fill >= 5) level(std::integral_constant<int, (T > 2 ? 5 : 1)>());
@@ -332,7 +359,7 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
 
 template <typename R, int T, int K, int NW, int WPE, int SITE, bool ZB, bool NORM>
 __global__ __launch_bounds__(NW * 64, WPE) void k3_march3r(FusedArgs<R> a, const R *__restrict__ tab, int tw) {
-    __shared__ cx<R> e[2 * 2 * T * 2 * NW * 64];
+    __shared__ cx<R> e[m3_edges<R, T, K, NW>()];
     __shared__ double red[NORM ? 2 * NW : 1];
     // each XCD (blocks are dealt to the eight in turn) takes a contiguous run of tiles
     const int n = gridDim.x, b = blockIdx.x, x = b & 7, q = n >> 3, r = n & 7;

@@ -63,6 +63,23 @@ __device__ __forceinline__ double t2_xp(double v) {
 template <typename C> __device__ __forceinline__ C t2_cxm(C v) { return mk2(t2_xm(v.x), t2_xm(v.y)); }
 template <typename C> __device__ __forceinline__ C t2_cxp(C v) { return mk2(t2_xp(v.x), t2_xp(v.y)); }
 
+// The Cayley coefficients of coef_theta(th), bit for bit, with the reciprocal of
+// 1 + th^2 written out: the hardware's estimate, two Newton steps and the residual
+// correction, which are the steps of an IEEE division whose operands need no
+// scaling (1 + th^2 is at least 1; the scaling, its undoing and the fix-up of
+// special operands are quarter-rate instructions).
+__device__ __forceinline__ Coef<double> coef_theta_r(double th) {
+    const double t2 = th * th, d = 1.0 + t2;
+    double y = __builtin_amdgcn_rcp(d);
+    y = fmx(y, fmx(-d, y, 1.0), y);
+    y = fmx(y, fmx(-d, y, 1.0), y);
+    const double r = fmx(fmx(-d, y, 1.0), y, y);
+    Coef<double> k;
+    k.c1 = mk2((1.0 - t2) * r, -((2.0 * th) * r));
+    k.c2 = mk2(r, -(th * r));
+    return k;
+}
+
 // Per-site coefficients as kept in registers: complex64 the record gamma;
 // complex128 alpha and Re beta, Im beta being half of Im alpha exactly.
 template <typename R> struct T2Site;
@@ -78,7 +95,7 @@ template <> struct T2Site<double> {
     double2 c1;
     double c2x;
     __device__ __forceinline__ void load(const double *th, size_t idx, double sgn) {
-        const Coef<double> k = coef_theta(sgn * th[idx]);
+        const Coef<double> k = coef_theta_r(sgn * th[idx]);
         c1 = k.c1;
         c2x = k.c2.x;
     }
