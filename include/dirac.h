@@ -408,6 +408,16 @@ int dirac_seed_region(dirac_ctx *ctx, double z0, void *const lam[], void *stream
 int dirac_adjoint_vz(dirac_ctx *ctx, int64_t n, void *const lam[], void *dLdV_int, void *dLdV_half,
                      void *stream);
 
+/* dirac_adjoint_vz with a second set of arrays for lam: work[] are 8 caller-owned
+ * device arrays shaped like lam, their contents lost, none of them a lam or state
+ * array (DIRAC_E_ARG), or work is NULL (dirac_adjoint_vz itself).  With them, on
+ * lattices large enough to gain, a backward step is one launch that ping-pongs the
+ * state between its two buffer sets and lam between lam[] and work[]; on return both are where
+ * dirac_adjoint_vz leaves them, with the same bits (the gradient: the same FP64
+ * terms, summed in another fixed order). */
+int dirac_adjoint_vz_work(dirac_ctx *ctx, int64_t n, void *const lam[], void *const work[], void *dLdV_int,
+                          void *dLdV_half, void *stream);
+
 /* The gradient of the region probability L = sum_{z_s >= z0} |psi_s|^2 after n
  * steps with respect to V(z): dirac_seed_region(ctx, z0, lam) then
  * dirac_adjoint_vz(ctx, n, lam, dLdV_int, dLdV_half).  lam: caller-owned work

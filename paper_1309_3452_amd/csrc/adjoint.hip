@@ -20,6 +20,9 @@
 // (sweep 3): lamY is then read and written once for both.  Per-(tile, plane) FP64 sums are
 // accumulated in place by the one workgroup owning them: no atomics, so the
 // gradient is bitwise reproducible.
+#include <algorithm>
+
+#include "adjmarch.h"
 #include "device.h"
 #include "internal.h"
 #include "stencil3.h"
@@ -38,12 +41,6 @@ template <typename R> __device__ __forceinline__ Coef<R> tcoef(const R *tab, int
     c.c2 = mk2(e[2], e[3]);
     return c;
 }
-
-__device__ __forceinline__ double2 alpha_of(const Coef<double> &k) { return k.c1; }
-__device__ __forceinline__ float2 alpha_of(const Coef<float> &k) { return mk2(1.0f - k.c1.x, -k.c1.y); }
-
-// conj(b) * z
-template <typename C> __device__ __forceinline__ C cmulc(C b, C z) { return cmul(cconj(b), z); }
 
 template <typename R, int SWEEP>
 __global__ __launch_bounds__(256) void k3_adj(AdjArgs<R> a) {
@@ -194,10 +191,15 @@ __global__ __launch_bounds__(256) void k_zero(double *p, int64_t n) {
 
 }  // namespace
 
-int adj_tiles3(int nx, int ny) { return ((nx + kTX - 1) / kTX) * ((ny + kTY - 1) / kTY); }
+// Slots per plane of the partial sums: the sweeps' tiles or the fused march's,
+// whichever are more.
+int adj_tiles3(int nx, int ny) {
+    return std::max(((nx + kTX - 1) / kTX) * ((ny + kTY - 1) / kTY), adj_march_tiles(nx, ny));
+}
+static int sweep_tiles(int nx, int ny) { return ((nx + kTX - 1) / kTX) * ((ny + kTY - 1) / kTY); }
 
 template <typename R> hipError_t launch_adj3(const AdjArgs<R> &a, int sweep, hipStream_t s) {
-    const int64_t nblk = (int64_t)adj_tiles3(a.nx, a.ny) * a.nz;
+    const int64_t nblk = (int64_t)sweep_tiles(a.nx, a.ny) * a.nz;
     if (nblk > 0x7fffffff) return hipErrorInvalidValue;
     dim3 g((unsigned)nblk), b(kTX * kTY);
     if (sweep == 0) hipLaunchKernelGGL((k3_adj<R, 0>), g, b, 0, s, a);

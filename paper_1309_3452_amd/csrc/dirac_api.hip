@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "../../include/dirac.h"
+#include "adjmarch.h"
 #include "cayley.h"
 #include "ctx.h"
 #include "gauge.h"
@@ -962,6 +963,11 @@ int dirac_adjoint(dirac_ctx *c, int64_t n, void *const lam[], double z0, void *d
 }
 
 int dirac_adjoint_vz(dirac_ctx *c, int64_t n, void *const lam[], void *dLdV_int, void *dLdV_half, void *stream) {
+    return dirac_adjoint_vz_work(c, n, lam, nullptr, dLdV_int, dLdV_half, stream);
+}
+
+int dirac_adjoint_vz_work(dirac_ctx *c, int64_t n, void *const lam[], void *const work[], void *dLdV_int,
+                          void *dLdV_half, void *stream) {
     int rc = check_ready(c, true);
     if (rc) return rc;
     if (c->ndim != 3) return fail(c, DIRAC_E_STATE, "the V(z) gradient is defined for 3D lattices");
@@ -974,6 +980,15 @@ int dirac_adjoint_vz(dirac_ctx *c, int64_t n, void *const lam[], void *dLdV_int,
     if (n < 0 || !lam || !dLdV_int || !dLdV_half) return fail(c, DIRAC_E_ARG, "bad arguments");
     for (int q = 0; q < 8; ++q)
         if (!lam[q]) return fail(c, DIRAC_E_ARG, "null lam array %d", q);
+    for (int q = 0; work && q < 8; ++q) {
+        if (!work[q]) return fail(c, DIRAC_E_ARG, "null work array %d", q);
+        for (int p = 0; p < 8; ++p)
+            if (work[q] == lam[p] || work[q] == c->buf[0][p] || work[q] == c->buf[1][p])
+                return fail(c, DIRAC_E_ARG, "work array %d is a state or lam array", q);
+    }
+    const uint64_t plane_bytes = (uint64_t)c->nx * (uint64_t)c->ny * (c->dtype == DIRAC_C64 ? 8u : 16u);
+    const bool march = work && plane_bytes < (1ull << 32) && !sets_shared(c) &&
+                       adj_march_wins(c->dtype == DIRAC_C64, (int)c->nx, (int)c->ny, (int)c->nz);
     hipStream_t s = (hipStream_t)stream;
     rc = upload_tables(c, s);
     if (rc) return rc;
@@ -999,11 +1014,31 @@ int dirac_adjoint_vz(dirac_ctx *c, int64_t n, void *const lam[], void *dLdV_int,
         a.nz = (int)c->nz;
         a.gpart = gpart;
         // sweeps 0, 1, 2 per backward step; sweep 2 of a step and sweep 0 of the
-        // next run as one launch (sweep 3)
+        // next run as one launch (sweep 3).  With a second set for lam, an even
+        // number of steps go one launch each, there and back.
+        const int64_t fused = march ? n & ~(int64_t)1 : 0;
         if (n > 0) HIPCHK(c, launch_adj3<R>(a, 0, s));
-        for (int64_t t = 0; t < n; ++t) {
+        for (int64_t t = 0; t < n - fused; ++t) {
             HIPCHK(c, launch_adj3<R>(a, 1, s));
             HIPCHK(c, launch_adj3<R>(a, t + 1 < n ? 3 : 2, s));
+        }
+        AdjMarchArgs<R> m;
+        memset(&m, 0, sizeof m);
+        m.rx = a.rx;
+        m.ry = a.ry;
+        m.rz = a.rz;
+        m.nx = a.nx;
+        m.ny = a.ny;
+        m.nz = a.nz;
+        m.gpart = gpart;
+        for (int64_t t = 0; t < fused; ++t) {
+            for (int q = 0; q < 8; ++q) {
+                m.f[q] = c->buf[t & 1 ? 1 - c->cur : c->cur][q];
+                m.fo[q] = c->buf[t & 1 ? c->cur : 1 - c->cur][q];
+                m.lam[q] = t & 1 ? work[q] : lam[q];
+                m.lamo[q] = t & 1 ? lam[q] : work[q];
+            }
+            HIPCHK(c, launch_adj_march<R>(m, a.tab_f, a.tab_r, t + 1 == fused, s));
         }
         return DIRAC_OK;
     };

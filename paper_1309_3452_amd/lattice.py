@@ -282,13 +282,16 @@ class Lattice:
                                       _stream_handle()), self._ctx)
         return lam
 
-    def adjoint_vz(self, n: int, lam):
-        """Backward through n steps from the current (final) state; see dirac_adjoint_vz."""
+    def adjoint_vz(self, n: int, lam, work=None):
+        """Backward through n steps from the current (final) state; see dirac_adjoint_vz.
+        work: 8 tensors like lam whose contents are lost; with them a step takes one
+        launch (dirac_adjoint_vz_work)."""
         dvi = torch.zeros(self.nz, dtype=torch.float64, device=self.device)
         dvh = torch.zeros(self.nz, dtype=torch.float64, device=self.device)
-        check(lib().dirac_adjoint_vz(self._ctx, int(n), ptr_array([t.data_ptr() for t in lam]),
-                                     ctypes.c_void_p(dvi.data_ptr()), ctypes.c_void_p(dvh.data_ptr()),
-                                     _stream_handle()), self._ctx)
+        check(lib().dirac_adjoint_vz_work(self._ctx, int(n), ptr_array([t.data_ptr() for t in lam]),
+                                          ptr_array([t.data_ptr() for t in work]) if work else None,
+                                          ctypes.c_void_p(dvi.data_ptr()), ctypes.c_void_p(dvh.data_ptr()),
+                                          _stream_handle()), self._ctx)
         return dvi, dvh
 
 
