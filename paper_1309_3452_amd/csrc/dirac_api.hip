@@ -255,7 +255,7 @@ bool march3_applies(const dirac_ctx *c) {
     if (plane_bytes >= (1ull << 32)) return false;
     if (!c->zbc && c->dtype == DIRAC_C64 && c->nx % 2 == 0) {
         const int nx = (int)c->nx, ny = (int)c->ny, nz = (int)c->nz;
-        if (march3r_us<float>(2, c->site_mode, nx, ny, nz) > 0.95 * march_lds_us(c->site_mode, nx, ny, nz)) return false;
+        if (march3r_us<float>(2, c->site_mode, false, nx, ny, nz) > 0.95 * march_lds_us(c->site_mode, nx, ny, nz)) return false;
     }
     return !sets_shared(c);
 }
@@ -288,7 +288,7 @@ template <typename R> bool plan_march3(const dirac_ctx *c, int64_t n, int64_t fl
     const int most = march3r_most(sizeof(R) == 4, c->site_mode);
     double us[4] = {};
     for (int t = 1; t <= most; ++t)
-        us[t] = march3r_us<R>(t, c->site_mode, (int)c->nx, (int)c->ny, (int)c->nz);
+        us[t] = march3r_us<R>(t, c->site_mode, c->zbc, (int)c->nx, (int)c->ny, (int)c->nz);
     bool found = false;
     double best = 0.0;
     const int64_t lo = (n + most - 1) / most, hi = n / 2 + 3 < n ? n / 2 + 3 : n;

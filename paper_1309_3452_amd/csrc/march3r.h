@@ -69,8 +69,9 @@ template <typename R, int T, int K, int NW> constexpr int m3_edges() {
 // records with theta -> -theta.  ZB: zero values outside the lattice (cells there
 // hold zero on every level).  e: m3_edges complex values of LDS.  nrm:
 // with NORM, this thread's sums of the functional (C,D-summed form) and the plain
-// norm.  A plane is below 4 GiB.
-template <typename R, int T, int K, int NW, int SITE, bool ZB, bool NORM>
+// norm.  XP: nx divides 64, the wave holds whole periods of a row and its shifts
+// rotate, so x takes no ring (one tile).  A plane is below 4 GiB.
+template <typename R, int T, int K, int NW, int SITE, bool ZB, bool NORM, bool XP>
 __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restrict__ tab, int tw, int tx, int ty,
                                         int z0, int z1, cx<R> *e, double (&nrm)[2]) {
     using C = cx<R>;
@@ -80,7 +81,7 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nx = a.nx, ny = a.ny, nz = a.nz, zh = a.zh;
     constexpr int th = NW * K - 2 * T;
-    const int rg = (64 - tw) / 2;
+    const int rg = XP ? 0 : (64 - tw) / 2;
     const int x0 = tx * tw, y0 = ty * th;
     const int w = min(tw, nx - x0), h = min(th, ny - y0);
     const int xl = x0 - rg + lane, yl = y0 - T + wv * K;
@@ -146,8 +147,8 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
     // loads for iteration h: the old second field of half-plane h and the old
     // first field of h-1 (ev: h is even); the records of the first field at h-1
     // and of the second at h-2, where levels 1 and 2 use them.  ds, df, dq: their
-    // planes behind kr.
-    auto load = [&](auto EV, auto DS, auto DF, auto DQ) __attribute__((always_inline)) {
+    // planes behind kr.  what: 1 the second field (and records), 2 the first, 3 both.
+    auto load = [&](auto EV, auto DS, auto DF, auto DQ, int what) __attribute__((always_inline)) {
         constexpr bool ev = decltype(EV)::value;
         constexpr int ds = decltype(DS)::value, df = decltype(DF)::value, dq = decltype(DQ)::value;
         const bool oks = inz(ds), okf = inz(df);
@@ -158,13 +159,17 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
             for (int k = 0; k < K; ++k) {
                 const char *bs = (const char *)a.in[(ev ? 6 : 4) + c] + ps, *bf = (const char *)a.in[(ev ? 2 : 0) + c] + pf;
                 if constexpr (ZB) {
-                    sn[c][k] = zero;
-                    fn[c][k] = zero;
-                    if (oks && in[k]) sn[c][k] = *(const C *)(bs + go[k]);
-                    if (okf && in[k]) fn[c][k] = *(const C *)(bf + go[k]);
+                    if (what & 1) {
+                        sn[c][k] = zero;
+                        if (oks && in[k]) sn[c][k] = *(const C *)(bs + go[k]);
+                    }
+                    if (what & 2) {
+                        fn[c][k] = zero;
+                        if (okf && in[k]) fn[c][k] = *(const C *)(bf + go[k]);
+                    }
                 } else {
-                    sn[c][k] = *(const C *)(bs + go[k]);
-                    fn[c][k] = *(const C *)(bf + go[k]);
+                    if (what & 1) sn[c][k] = *(const C *)(bs + go[k]);
+                    if (what & 2) fn[c][k] = *(const C *)(bf + go[k]);
                 }
             }
         if constexpr (SITE != 0) {
@@ -207,10 +212,16 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
             }
 #pragma unroll
         for (int k = 0; k < K; ++k) asm volatile("" : "+v"(go[k]));
-        // next, for h = 2k: C and A of plane k; for h = 2k+1: D of plane k+1, B of k
-        if (hh < he)
-            load(std::integral_constant<bool, (ph & 1) == 1>(), std::integral_constant<int, (ph & 1) ? -1 : 0>(),
-                 std::integral_constant<int, 0>(), std::integral_constant<int, (ph & 1) ? 0 : 1>());
+        // next, for h = 2k: C and A of plane k; for h = 2k+1: D of plane k+1, B of k.
+        // With tables the first field's loads go out after level 2: spread over the
+        // iteration they cost 2 to 6% less time than in one burst (256^3 complex64
+        // 271 against 281 us per step; with records 17% more, so there they stay).
+        auto next = [&](int what) __attribute__((always_inline)) {
+            if (hh < he)
+                load(std::integral_constant<bool, (ph & 1) == 1>(), std::integral_constant<int, (ph & 1) ? -1 : 0>(),
+                     std::integral_constant<int, 0>(), std::integral_constant<int, (ph & 1) ? 0 : 1>(), what);
+        };
+        next(SITE == 0 ? 1 : 3);
         // edges of level l's newest half-plane, of this iteration or (ago = 1) the last
         auto put = [&](auto LV, int ago) __attribute__((always_inline)) {
             constexpr int l = decltype(LV)::value;
@@ -223,6 +234,8 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
         } else {
             put(std::integral_constant<int, 0>(), 0);
         }
+        auto xm = [](C v) __attribute__((always_inline)) { return XP ? t2_rxm(v) : t2_cxm(v); };
+        auto xp = [](C v) __attribute__((always_inline)) { return XP ? t2_rxp(v) : t2_cxp(v); };
         auto level = [&](auto LV) __attribute__((always_inline)) {
             constexpr int l = decltype(LV)::value;
             constexpr bool first = l & 1;                            // the first field (A, B)
@@ -250,18 +263,18 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
                 const C m1ym = k > 0 ? W[l - 1][sm][1][k > 0 ? k - 1 : 0] : dn;
                 const C m0yp = k + 1 < K ? W[l - 1][sm][0][k + 1 < K ? k + 1 : 0] : up;
                 if constexpr (rowP) {
-                    S[0][k] = sterm3(rz, dz0, rx, csub(m0, t2_cxm(m0)), -ry, csub(m1, m1ym));
-                    S[1][k] = sterm3(rz, dz1, rx, csub(t2_cxp(m1), m1), -ry, csub(m0yp, m0));
+                    S[0][k] = sterm3(rz, dz0, rx, csub(m0, xm(m0)), -ry, csub(m1, m1ym));
+                    S[1][k] = sterm3(rz, dz1, rx, csub(xp(m1), m1), -ry, csub(m0yp, m0));
                 } else {
-                    S[0][k] = sterm3(-rz, dz0, rx, csub(t2_cxp(m0), m0), ry, csub(m1, m1ym));
-                    S[1][k] = sterm3(-rz, dz1, rx, csub(m1, t2_cxm(m1)), ry, csub(m0yp, m0));
+                    S[0][k] = sterm3(-rz, dz0, rx, csub(xp(m0), m0), ry, csub(m1, m1ym));
+                    S[1][k] = sterm3(-rz, dz1, rx, csub(m1, xm(m1)), ry, csub(m0yp, m0));
                 }
                 if constexpr (wide) {
                     auto d = [](C p, C q) { return make_double2((double)p.x - (double)q.x, (double)p.y - (double)q.y); };
                     const C *z0p = &W[l - 1][sp][0][k], *z0m = &W[l - 1][so][0][k];
                     const C *z1p = &W[l - 1][sp][1][k], *z1m = &W[l - 1][so][1][k];
                     const double dx = rx, dy = rowP ? -(double)ry : (double)ry, dz = rowP ? (double)rz : -(double)rz;
-                    const C xa = rowP ? t2_cxm(m0) : t2_cxp(m0), xb = rowP ? t2_cxp(m1) : t2_cxm(m1);
+                    const C xa = rowP ? xm(m0) : xp(m0), xb = rowP ? xp(m1) : xm(m1);
                     Sd[0][wide ? k : 0] = sterm3(dz, d(*z0p, *z0m), dx, rowP ? d(m0, xa) : d(xa, m0), dy, d(m1, m1ym));
                     Sd[wide ? 1 : 0][wide ? k : 0] =
                         sterm3(dz, d(*z1p, *z1m), dx, rowP ? d(xb, m1) : d(m1, xb), dy, d(m0yp, m0));
@@ -315,6 +328,7 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
         };
         if constexpr (fill >= 1) level(std::integral_constant<int, 1>());
         if constexpr (fill >= 2) level(std::integral_constant<int, 2>());
+        if constexpr (SITE == 0) next(2);
         if constexpr (SB) {
             asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
             put(std::integral_constant<int, 0>(), 0);
@@ -335,7 +349,7 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
 
     // for h = hs = 2k: D of plane k, B of k-1
     load(std::integral_constant<bool, true>(), std::integral_constant<int, 0>(), std::integral_constant<int, 1>(),
-         std::integral_constant<int, 1>());
+         std::integral_constant<int, 1>(), 3);
     // 2 (z1 - z0) + 4 T iterations: an even number, at least six
     constexpr std::true_type filling{};
     constexpr std::false_type full{};
@@ -357,7 +371,7 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
     }
 }
 
-template <typename R, int T, int K, int NW, int WPE, int SITE, bool ZB, bool NORM>
+template <typename R, int T, int K, int NW, int WPE, int SITE, bool ZB, bool NORM, bool XP>
 __global__ __launch_bounds__(NW * 64, WPE) void k3_march3r(FusedArgs<R> a, const R *__restrict__ tab, int tw) {
     __shared__ cx<R> e[m3_edges<R, T, K, NW>()];
     __shared__ double red[NORM ? 2 * NW : 1];
@@ -366,7 +380,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void k3_march3r(FusedArgs<R> a, const
     const int L = x * q + min(x, r) + (b >> 3);
     const int tx = L % a.ntx, ty = L / a.ntx % a.nty, zc = L / (a.ntx * a.nty);
     double nrm[2] = {0.0, 0.0};
-    march3r<R, T, K, NW, SITE, ZB, NORM>(a, tab, tw, tx, ty, zc * a.zchunk, min(a.nz, (zc + 1) * a.zchunk), e, nrm);
+    march3r<R, T, K, NW, SITE, ZB, NORM, XP>(a, tab, tw, tx, ty, zc * a.zchunk, min(a.nz, (zc + 1) * a.zchunk), e, nrm);
     if constexpr (NORM) {
         const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
@@ -396,6 +410,7 @@ struct M3Shape {
 // chunks in z, and its estimated time.
 struct M3Pick {
     int shape = -1, tw = 0, nty = 0, nzc = 0;
+    bool xp = false;                        // rows wrap within the wave
     double us = 0.0;
 };
 
@@ -410,15 +425,18 @@ inline int m3_width(int nx, int T) {
 // The fastest of `count` shapes for T steps.  A chunk of p planes takes 2 p + 4 T
 // iterations, of which the filling ones evaluate few levels: together they cost
 // about 2 (p + T).  Workgroups run in rounds of one or two per CU.  The last pick
-// for each (T, records) is kept per thread.
-inline const M3Pick &m3_pick(const M3Shape *sh, int count, int T, bool rec, int nx, int ny, int nz) {
+// for each (T, records, boundary) is kept per thread.  Periodic rows that divide 64
+// need no ring in x: built for the shapes of one row per thread and two steps, which
+// such lattices take (two steps of 64^3: complex64 17.1 against 21 us, complex128
+// 21.7 against 28, with records 28 against 39).
+inline const M3Pick &m3_pick(const M3Shape *sh, int count, int T, bool rec, bool zb, int nx, int ny, int nz) {
     struct Memo {
         int nx = -1, ny = -1, nz = -1;
         const M3Shape *sh = nullptr;
         M3Pick pick;
     };
-    static thread_local Memo memo[4][2];
-    Memo &m = memo[T & 3][rec ? 1 : 0];
+    static thread_local Memo memo[4][4];
+    Memo &m = memo[T & 3][(rec ? 1 : 0) | (zb ? 2 : 0)];
     if (m.sh == sh && m.nx == nx && m.ny == ny && m.nz == nz) return m.pick;
     M3Pick best;
     const int64_t cus = resident_per_round();
@@ -426,7 +444,8 @@ inline const M3Pick &m3_pick(const M3Shape *sh, int count, int T, bool rec, int 
         if (sh[q].T != T) continue;
         M3Pick p;
         p.shape = q;
-        p.tw = m3_width(nx, T);
+        p.xp = !zb && T == 2 && sh[q].K == 1 && 64 % nx == 0;
+        p.tw = p.xp ? nx : m3_width(nx, T);
         p.nty = (ny + sh[q].K * sh[q].NW - 2 * T - 1) / (sh[q].K * sh[q].NW - 2 * T);
         const int64_t tiles = (int64_t)((nx + p.tw - 1) / p.tw) * p.nty;
         for (int occ = 1; occ <= sh[q].occ; ++occ) {
@@ -461,7 +480,14 @@ hipError_t m3_launch(FusedArgs<R> a, const M3Pick &pick, bool zb, hipStream_t s,
     const bool norm = a.npart != nullptr;
     if (norm && (nblk > a.npart_cap || a.rev || T > 2)) return hipErrorInvalidValue;
     const dim3 g((unsigned)nblk), b(NW * 64);
-#define M3(SITE, ZB, NORM) hipLaunchKernelGGL((k3_march3r<R, T, K, NW, WPE, SITE, ZB, NORM>), g, b, 0, s, a, a.tab, tw)
+#define M3(SITE, ZB, NORM)                                                                                          \
+    do {                                                                                                            \
+        constexpr bool XP = !ZB && T == 2 && K == 1;                                                                \
+        if (XP && pick.xp)                                                                                          \
+            hipLaunchKernelGGL((k3_march3r<R, T, K, NW, WPE, SITE, ZB, NORM, XP>), g, b, 0, s, a, a.tab, tw);       \
+        else                                                                                                        \
+            hipLaunchKernelGGL((k3_march3r<R, T, K, NW, WPE, SITE, ZB, NORM, false>), g, b, 0, s, a, a.tab, tw);    \
+    } while (0)
     if constexpr (T > 2) {
         if (zb) M3(0, true, false);
         else M3(0, false, false);

@@ -12,19 +12,19 @@ constexpr M3Shape kTab[] = {{1, 4, 8, 1, 5.0}, {2, 2, 16, 1, 4.6}, {2, 1, 16, 1,
 constexpr M3Shape kSite[] = {{1, 2, 8, 1, 3.6}, {2, 2, 8, 1, 3.3}, {2, 1, 8, 1, 1.25}};
 constexpr int kNTab = sizeof(kTab) / sizeof(kTab[0]), kNSite = sizeof(kSite) / sizeof(kSite[0]);
 
-const M3Pick &pick(int steps, bool site, int nx, int ny, int nz) {
-    return m3_pick(site ? kSite : kTab, site ? kNSite : kNTab, steps, site, nx, ny, nz);
+const M3Pick &pick(int steps, bool site, bool zb, int nx, int ny, int nz) {
+    return m3_pick(site ? kSite : kTab, site ? kNSite : kNTab, steps, site, zb, nx, ny, nz);
 }
 }  // namespace
 
-template <> double march3r_us<float>(int steps, bool site, int nx, int ny, int nz) {
-    return pick(steps, site, nx, ny, nz).us;
+template <> double march3r_us<float>(int steps, bool site, bool zb, int nx, int ny, int nz) {
+    return pick(steps, site, zb, nx, ny, nz).us;
 }
 
 template <>
 hipError_t launch_march3r<float>(const FusedArgs<float> &a, int steps, bool site, bool zb, hipStream_t s,
                                  int *nblocks_out) {
-    const M3Pick &p = pick(steps, site, a.nx, a.ny, a.nz);
+    const M3Pick &p = pick(steps, site, zb, a.nx, a.ny, a.nz);
     const int q = p.shape;
     if (site) {
         if (q == 0) return m3_launch<float, 1, 2, 8, 2, true>(a, p, zb, s, nblocks_out);

@@ -10,7 +10,7 @@ int resident_per_round();              // workgroups of one per CU (fused2.hip)
 // Most steps of one launch: three only with V(z) tables in complex64.
 inline int march3r_most(bool fp32, bool site) { return fp32 && !site ? 3 : 2; }
 // Estimated microseconds of a launch of `steps` steps.
-template <typename R> double march3r_us(int steps, bool site, int nx, int ny, int nz);
+template <typename R> double march3r_us(int steps, bool site, bool zb, int nx, int ny, int nz);
 // The same for two steps of the LDS march on complex64 lattices of even width
 // (fused2.hip): its workgroups spend about 3.3 us on a plane, 5.4 with records.
 inline double march_lds_us(bool site, int nx, int ny, int nz) {

@@ -63,6 +63,20 @@ __device__ __forceinline__ double t2_xp(double v) {
 template <typename C> __device__ __forceinline__ C t2_cxm(C v) { return mk2(t2_xm(v.x), t2_xm(v.y)); }
 template <typename C> __device__ __forceinline__ C t2_cxp(C v) { return mk2(t2_xp(v.x), t2_xp(v.y)); }
 
+// The same around the wave: the first lane's lower neighbour is the last lane.
+__device__ __forceinline__ int t2_rot_below(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x13c, 0xf, 0xf, true); }
+__device__ __forceinline__ int t2_rot_above(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x134, 0xf, 0xf, true); }
+__device__ __forceinline__ float t2_rm(float v) { return __int_as_float(t2_rot_below(__float_as_int(v))); }
+__device__ __forceinline__ float t2_rp(float v) { return __int_as_float(t2_rot_above(__float_as_int(v))); }
+__device__ __forceinline__ double t2_rm(double v) {
+    return __hiloint2double(t2_rot_below(__double2hiint(v)), t2_rot_below(__double2loint(v)));
+}
+__device__ __forceinline__ double t2_rp(double v) {
+    return __hiloint2double(t2_rot_above(__double2hiint(v)), t2_rot_above(__double2loint(v)));
+}
+template <typename C> __device__ __forceinline__ C t2_rxm(C v) { return mk2(t2_rm(v.x), t2_rm(v.y)); }
+template <typename C> __device__ __forceinline__ C t2_rxp(C v) { return mk2(t2_rp(v.x), t2_rp(v.y)); }
+
 // The Cayley coefficients of coef_theta(th), bit for bit, with the reciprocal of
 // 1 + th^2 written out: the hardware's estimate, two Newton steps and the residual
 // correction, which are the steps of an IEEE division whose operands need no

@@ -30,7 +30,7 @@ def same(a, b):
 
 
 CASES = [((1, 1, 1), 5), ((3, 2, 2), 9), ((5, 4, 3), 4), ((57, 13, 5), 7), ((61, 30, 4), 6), ((121, 29, 33), 10),
-         ((64, 64, 40), 11), ((113, 57, 130), 5)]
+         ((64, 64, 40), 11), ((113, 57, 130), 5), ((64, 13, 7), 6), ((32, 21, 9), 4), ((16, 16, 16), 5), ((2, 9, 30), 4)]
 
 
 @pytest.mark.parametrize("dtype", [torch.complex64, torch.complex128])
