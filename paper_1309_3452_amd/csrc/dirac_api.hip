@@ -399,6 +399,15 @@ template <typename R> int run_tile2(dirac_ctx *c, int64_t n, bool reverse, int64
     return DIRAC_OK;
 }
 
+// Two steps of a (3+1)D lattice or z-slab in one launch: in complex128 a slab takes
+// the register march too, whose two-step reach is the slab's two halo planes
+// (512 x 512 x 64: 0.90 against 1.08 ms, with records 1.45 against 1.91).
+template <typename R> hipError_t launch_two(const dirac_ctx *c, const FusedArgs<R> &a, hipStream_t s, int *nblocks) {
+    if (sizeof(R) == 8 && c->zh && c->kernel == DIRAC_KERNEL_AUTO && c->zchunk == 0)
+        return launch_march3r<R>(a, 2, c->site_mode, false, s, nblocks);
+    return launch_fused3x2<R>(a, c->site_mode, s, nblocks);
+}
+
 template <typename R> int run_steps(dirac_ctx *c, int64_t n, bool reverse, hipStream_t s) {
     int rc = upload_tables(c, s);
     if (rc) return rc;
@@ -418,7 +427,7 @@ template <typename R> int run_steps(dirac_ctx *c, int64_t n, bool reverse, hipSt
     if (kc == DIRAC_KERNEL_FUSED2) {
         for (; t + 2 <= n; t += 2) {
             FusedArgs<R> a = fused_args<R>(c);
-            if (c->ndim == 3) HIPCHK(c, launch_fused3x2<R>(a, site, s));
+            if (c->ndim == 3) HIPCHK(c, launch_two<R>(c, a, s, nullptr));
             else HIPCHK(c, launch_fused2x2<R>(a, site, s));
             c->cur = 1 - c->cur;
         }
@@ -803,12 +812,12 @@ int dirac_step_norm(dirac_ctx *c, int64_t n, void *dev_out, void *stream) {
             FusedArgs<float> a = fused_args<float>(c);
             a.npart = part;
             a.npart_cap = cap;
-            e = launch_fused3x2<float>(a, c->site_mode, s, &nb);
+            e = launch_two<float>(c, a, s, &nb);
         } else {
             FusedArgs<double> a = fused_args<double>(c);
             a.npart = part;
             a.npart_cap = cap;
-            e = launch_fused3x2<double>(a, c->site_mode, s, &nb);
+            e = launch_two<double>(c, a, s, &nb);
         }
         if (e == hipSuccess) {
             c->cur = 1 - c->cur;

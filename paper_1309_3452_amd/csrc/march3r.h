@@ -425,19 +425,18 @@ inline int m3_width(int nx, int T) {
 // The fastest of `count` shapes for T steps.  A chunk of p planes takes 2 p + 4 T
 // iterations, of which the filling ones evaluate few levels: together they cost
 // about 2 (p + T).  Workgroups run in rounds of one or two per CU.  The last pick
-// for each (T, records, boundary) is kept per thread.  Periodic rows that divide 64
+// for each (T, boundary) is kept per thread.  Periodic rows that divide 64
 // need no ring in x: built for the shapes of one row per thread and two steps, which
 // such lattices take (two steps of 64^3: complex64 17.1 against 21 us, complex128
 // 21.7 against 28, with records 28 against 39).
-inline const M3Pick &m3_pick(const M3Shape *sh, int count, int T, bool rec, bool zb, int nx, int ny, int nz) {
+static const M3Pick &m3_pick(const M3Shape *sh, int count, int T, bool zb, int nx, int ny, int nz) {
     struct Memo {
         int nx = -1, ny = -1, nz = -1;
-        const M3Shape *sh = nullptr;
         M3Pick pick;
     };
-    static thread_local Memo memo[4][4];
-    Memo &m = memo[T & 3][(rec ? 1 : 0) | (zb ? 2 : 0)];
-    if (m.sh == sh && m.nx == nx && m.ny == ny && m.nz == nz) return m.pick;
+    static thread_local Memo memo[4][2];
+    Memo &m = memo[T & 3][zb ? 1 : 0];
+    if (m.nx == nx && m.ny == ny && m.nz == nz) return m.pick;
     M3Pick best;
     const int64_t cus = resident_per_round();
     for (int q = 0; q < count; ++q) {
@@ -458,7 +457,6 @@ inline const M3Pick &m3_pick(const M3Shape *sh, int count, int T, bool rec, bool
             }
         }
     }
-    m.sh = sh;
     m.nx = nx;
     m.ny = ny;
     m.nz = nz;

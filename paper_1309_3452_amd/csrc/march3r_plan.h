@@ -9,8 +9,11 @@ namespace dirac {
 int resident_per_round();              // workgroups of one per CU (fused2.hip)
 // Most steps of one launch: three only with V(z) tables in complex64.
 inline int march3r_most(bool fp32, bool site) { return fp32 && !site ? 3 : 2; }
-// Estimated microseconds of a launch of `steps` steps.
-template <typename R> double march3r_us(int steps, bool site, bool zb, int nx, int ny, int nz);
+// Estimated microseconds of a launch of `steps` steps (REC: with per-site records).
+template <typename R, bool REC> double march3r_us_of(int steps, bool zb, int nx, int ny, int nz);
+template <typename R> double march3r_us(int steps, bool site, bool zb, int nx, int ny, int nz) {
+    return site ? march3r_us_of<R, true>(steps, zb, nx, ny, nz) : march3r_us_of<R, false>(steps, zb, nx, ny, nz);
+}
 // The same for two steps of the LDS march on complex64 lattices of even width
 // (fused2.hip): its workgroups spend about 3.3 us on a plane, 5.4 with records.
 inline double march_lds_us(bool site, int nx, int ny, int nz) {
@@ -22,7 +25,12 @@ inline double march_lds_us(bool site, int nx, int ny, int nz) {
 // One launch of `steps` steps, in -> out, forward or (a.rev) of the reversed
 // sequence.  With a.npart (one or two steps, forward) the per-workgroup sums of
 // the functional go there.
+template <typename R, bool REC>
+hipError_t launch_march3r_of(const FusedArgs<R> &a, int steps, bool zb, hipStream_t s, int *nblocks_out);
 template <typename R>
-hipError_t launch_march3r(const FusedArgs<R> &a, int steps, bool site, bool zb, hipStream_t s, int *nblocks_out = nullptr);
+hipError_t launch_march3r(const FusedArgs<R> &a, int steps, bool site, bool zb, hipStream_t s, int *nblocks_out = nullptr) {
+    return site ? launch_march3r_of<R, true>(a, steps, zb, s, nblocks_out)
+                : launch_march3r_of<R, false>(a, steps, zb, s, nblocks_out);
+}
 
 }  // namespace dirac
