@@ -273,7 +273,8 @@ int dirac_coef_from_theta_c(void *coef, const void *theta, const void *theta_im,
  * links keep E_r (dirac_norm, evaluated with the links) exactly conserved.
  * While links are bound, a step takes one launch (a z-march in 3D, a y-march in
  * 2D) that moves the state to the other buffer set, unless DIRAC_KERNEL_SPLIT
- * is set; the reversed step and DIRAC_KERNEL_SPLIT use the in-place split
+ * is set (in 2D with DIRAC_KERNEL_AUTO several steps share a launch, the set that
+ * ends up with the state being the same); the reversed step and DIRAC_KERNEL_SPLIT use the in-place split
  * kernels; all give the same bits.  dirac_step_norm steps, then reduces.
  * dirac_adjoint_vz is refused.  links == NULL unbinds them.  The arrays must stay valid while
  * bound.  DIRAC_E_ARG for a null link array (nothing is bound then),

@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libdirac.so")
 BUILD = os.path.join(ROOT, "_build")
 SOURCES = ["dirac_api.hip", "kernels3d.hip", "kernels2d.hip", "fused.hip", "fused2.hip", "adjoint.hip", "batch.hip", "gauge.hip",
-           "noalloc.hip", "norm3.hip", "probe.hip", "tile2.hip",
+           "noalloc.hip", "norm3.hip", "probe.hip", "tile2.hip", "tile2links.hip",
            "march3r_c64.hip", "march3r_c64_site.hip", "march3r_c128.hip", "march3r_c128_site.hip",
            "adjmarch.hip"]
 ARCH = os.environ.get("DIRAC_OFFLOAD_ARCH", "gfx950")

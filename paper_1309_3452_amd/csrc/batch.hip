@@ -439,10 +439,10 @@ struct BRun {
 void plan_tiles(const dirac_ctx *c, int64_t n, BRun *r) {
     const bool fp32 = c->dtype == DIRAC_C64;
     const int64_t flips = two_step_ok(c) ? n / 2 + (n & 1) : n;
-    r->passes = tile2_passes(n, (int)(flips & 1), c->count, c->bnx.data(), c->bny.data(), fp32, true);
+    r->passes = tile2_passes(n, (int)(flips & 1), c->count, c->bnx.data(), c->bny.data(), fp32, tile2_kind(true, false));
     r->ring = r->passes > 0 ? (int)((n + r->passes - 1) / r->passes) : 1;
     double us = 0.0;
-    r->shape = tile2_best_shape(r->ring, c->count, c->bnx.data(), c->bny.data(), fp32, true, &us);
+    r->shape = tile2_best_shape(r->ring, c->count, c->bnx.data(), c->bny.data(), fp32, tile2_kind(true, false), &us);
 }
 
 // Upload lattice descriptors and the item list of choice q for n steps.

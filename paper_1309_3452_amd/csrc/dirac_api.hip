@@ -235,7 +235,7 @@ bool sets_shared(const dirac_ctx *c) {
 // (2+1)D with the kernel and its knobs left to the library: several steps per
 // pass on register tiles (tile2.hip).
 bool tile2_applies(const dirac_ctx *c) {
-    return c->ndim == 2 && c->kernel == DIRAC_KERNEL_AUTO && c->zchunk == 0 && !c->links_on && !sets_shared(c);
+    return c->ndim == 2 && c->kernel == DIRAC_KERNEL_AUTO && c->zchunk == 0 && !sets_shared(c);
 }
 
 // (3+1)D likewise: the register march (march3r.h) where it is the fastest kernel.
@@ -389,11 +389,14 @@ template <typename R> int run_reverse_march(dirac_ctx *c, int64_t n, hipStream_t
 // n steps on register tiles with `flips` mod 2 buffer-set flips; *done false
 // where there is no such split of n (then nothing was launched).
 template <typename R> int run_tile2(dirac_ctx *c, int64_t n, bool reverse, int64_t flips, hipStream_t s, bool *done) {
-    const int64_t passes = tile2_passes(n, (int)(flips & 1), 1, &c->nx, &c->ny, sizeof(R) == 4, c->site_mode);
+    const int64_t passes = tile2_passes(n, (int)(flips & 1), 1, &c->nx, &c->ny, sizeof(R) == 4,
+                                        tile2_kind(c->site_mode, c->links_on));
     *done = passes > 0;
     for (int64_t p = 0; p < passes; ++p) {
         const FusedArgs<R> a = reverse ? fused_args_rev<R>(c) : fused_args<R>(c);
-        HIPCHK(c, launch_tile2<R>(a, c->site_mode, c->zbc, (int)(n / passes + (p < n % passes)), s));
+        const int steps = (int)(n / passes + (p < n % passes));
+        HIPCHK(c, c->links_on ? launch_tile2_links<R>(a, link_ptrs(c), c->site_mode, steps, s)
+                              : launch_tile2<R>(a, c->site_mode, c->zbc, steps, s));
         c->cur = 1 - c->cur;
     }
     return DIRAC_OK;
@@ -411,7 +414,7 @@ template <typename R> hipError_t launch_two(const dirac_ctx *c, const FusedArgs<
 template <typename R> int run_steps(dirac_ctx *c, int64_t n, bool reverse, hipStream_t s) {
     int rc = upload_tables(c, s);
     if (rc) return rc;
-    if (tile2_applies(c)) {
+    if (tile2_applies(c) && !(reverse && c->links_on)) {
         bool done = false;
         rc = run_tile2<R>(c, n, reverse, reverse ? 0 : flips_of(c, n), s, &done);
         if (rc || done) return rc;

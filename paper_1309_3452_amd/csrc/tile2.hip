@@ -47,35 +47,38 @@ int64_t tile2_tiles(int shape, int ring, int64_t nx, int64_t ny) {
 // Microseconds of one pass of `steps` steps over `tiles` tiles holding `cells`
 // lattice cells: a launch costs 3.2; a CU evaluates a region cell in 0.66 ns
 // (complex64), 0.85 ns (complex128) or 1.4 ns (complex128 per site, one workgroup
-// per CU), counting whole rounds while there are few, 1.6 times that where eight
+// per CU), with links 2.2 times that, counting whole rounds while there are few, 1.6 times that where eight
 // waves have a CU to themselves; the bytes of one pass go at 5 TB/s, 9 out of the
 // caches.  Both overlap, the longer one only in part (cube root of the sum of
 // cubes: 2047 x 1531 complex64 per site measured 77, 84, 105 us for 5, 6, 7 steps
 // with 62, 82, 105 us of arithmetic and 60 of bytes).
-double tile2_pass_us(int shape, int steps, int64_t tiles, double cells, bool fp32, bool site) {
+double tile2_pass_us(int shape, int steps, int64_t tiles, double cells, bool fp32, int kind) {
     const double cus = resident_per_round();
+    const bool site = kind & 1, links = kind & 2;
     double per = (double)tiles / cus;
     if (per <= 4.0) per = (double)((tiles + (int64_t)cus - 1) / (int64_t)cus);
     double rows = (double)tile2_rows(shape) * steps;
     if (shape == 0) rows -= (double)steps * (steps - 1);          // the waves that skip
-    const double cell_ns = (fp32 ? 0.66 : site ? 1.4 : 0.85) * (shape == 2 && per < 2.0 ? 1.6 : 1.0);
+    const double cell_ns = (fp32 ? 0.66 : site ? 1.4 : 0.85) * (shape == 2 && per < 2.0 ? 1.6 : 1.0) * (links ? 2.2 : 1.0);
     const double comp = per * rows * 64.0 * cell_ns * 1e-3;
-    const double bytes = cells * ((fp32 ? 64.0 : 128.0) + (site ? 32.0 : 0.0));
+    const double bytes = cells * ((fp32 ? 64.0 : 128.0) + (site ? 32.0 : 0.0) + (links ? (fp32 ? 64.0 : 128.0) : 0.0));
     const double mem = bytes / (bytes > 2e8 ? 5e6 : 9e6);
     return 3.2 + cbrt(comp * comp * comp + mem * mem * mem);
 }
 
-int tile2_best_shape(int steps, int64_t count, const int64_t *nx, const int64_t *ny, bool fp32, bool site, double *us) {
+int tile2_best_shape(int steps, int64_t count, const int64_t *nx, const int64_t *ny, bool fp32, int kind, double *us) {
     int best = -1;
     for (int shape = 0; shape < 3; ++shape) {
-        if ((shape == 2 && site && !fp32) || tile2_rows(shape) - 2 * steps < 2) continue;
+        if (shape == 2 && ((kind & 2) || ((kind & 1) && !fp32))) continue;      // not built: registers
+        if (shape == 1 && (kind & 2) && !fp32) continue;
+        if (tile2_rows(shape) - 2 * steps < 2) continue;
         int64_t tiles = 0;
         double cells = 0.0;
         for (int64_t b = 0; b < count; ++b) {
             tiles += tile2_tiles(shape, steps, nx[b], ny[b]);
             cells += (double)nx[b] * (double)ny[b];
         }
-        const double t = tile2_pass_us(shape, steps, tiles, cells, fp32, site);
+        const double t = tile2_pass_us(shape, steps, tiles, cells, fp32, kind);
         if (best < 0 || t < *us) {
             best = shape;
             *us = t;
@@ -88,11 +91,11 @@ int tile2_best_shape(int steps, int64_t count, const int64_t *nx, const int64_t 
 // whose parity is that of `parity` (the passes ping-pong between two buffer sets,
 // and the set that ends up with the state is part of the call's result); 0 where
 // there is none (n = 1 with an even count).
-int64_t tile2_passes(int64_t n, int parity, int64_t count, const int64_t *nx, const int64_t *ny, bool fp32, bool site) {
+int64_t tile2_passes(int64_t n, int parity, int64_t count, const int64_t *nx, const int64_t *ny, bool fp32, int kind) {
     int64_t best = 0;
     double best_us = 0.0, us[kTile2MaxSteps + 1] = {};
     for (int t = 1; t <= kTile2MaxSteps && t <= n; ++t) {
-        tile2_best_shape(t, count, nx, ny, fp32, site, &us[t]);
+        if (tile2_best_shape(t, count, nx, ny, fp32, kind, &us[t]) < 0) break;
         int64_t p = (n + t - 1) / t;
         if ((p ^ parity) & 1) ++p;
         if (p > n) continue;
@@ -112,7 +115,8 @@ hipError_t launch_tile2(const FusedArgs<R> &a0, bool site, bool zb, int steps, h
     if (steps < 1 || steps > kTile2MaxSteps || (!site && a.tab == nullptr)) return hipErrorInvalidValue;
     const int64_t nx = a.nx, ny = a.ny;
     double us = 0.0;
-    const int shape = tile2_best_shape(steps, 1, &nx, &ny, sizeof(R) == 4, site, &us);
+    const int shape = tile2_best_shape(steps, 1, &nx, &ny, sizeof(R) == 4, tile2_kind(site, false), &us);
+    if (shape < 0) return hipErrorInvalidValue;
     const int64_t tiles = tile2_tiles(shape, steps, nx, ny);
     if (tiles > 0x7fffffff) return hipErrorInvalidValue;
     a.ntx = (a.nx + 64 - 2 * steps - 1) / (64 - 2 * steps);

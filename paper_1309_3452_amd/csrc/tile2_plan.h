@@ -8,14 +8,19 @@ namespace dirac {
 
 constexpr int kTile2MaxSteps = 8;      // most steps of one pass
 int resident_per_round();              // workgroups of one per CU (fused2.hip)
+// What a cell carries beside its amplitudes: bit 0 per-site records, bit 1 links.
+inline int tile2_kind(bool site, bool links) { return (site ? 1 : 0) | (links ? 2 : 0); }
 int tile2_rows(int shape);             // rows of a tile shape's region
 int64_t tile2_tiles(int shape, int ring, int64_t nx, int64_t ny);
 // estimated microseconds of a pass
-double tile2_pass_us(int shape, int steps, int64_t tiles, double cells, bool fp32, bool site);
+double tile2_pass_us(int shape, int steps, int64_t tiles, double cells, bool fp32, int kind);
 // the fastest shape for a pass of `steps` over `count` lattices, and its time
-int tile2_best_shape(int steps, int64_t count, const int64_t *nx, const int64_t *ny, bool fp32, bool site, double *us);
+int tile2_best_shape(int steps, int64_t count, const int64_t *nx, const int64_t *ny, bool fp32, int kind, double *us);
 // passes for n steps with the parity of `parity`; 0 if there is no such split
-int64_t tile2_passes(int64_t n, int parity, int64_t count, const int64_t *nx, const int64_t *ny, bool fp32, bool site);
+int64_t tile2_passes(int64_t n, int parity, int64_t count, const int64_t *nx, const int64_t *ny, bool fp32, int kind);
 template <typename R> hipError_t launch_tile2(const FusedArgs<R> &a, bool site, bool zb, int steps, hipStream_t s);
+// The same with gauge links (tile2links.hip), periodic and forward.
+template <typename R>
+hipError_t launch_tile2_links(const FusedArgs<R> &a, const LinkPtrs &L, bool site, int steps, hipStream_t s);
 
 }  // namespace dirac

@@ -64,6 +64,30 @@ def test_tiles_bitwise_equal_split(P, dtype, site, zero, shape, steps):
     assert same(lats[0].state(), lats[1].state()) and torch.equal(a, b)
 
 
+@pytest.mark.parametrize("dtype", [torch.complex64, torch.complex128])
+@pytest.mark.parametrize("site", [False, True])
+@pytest.mark.parametrize("shape,steps", [((1, 1), 4), ((5, 3), 9), ((51, 4), 7), ((129, 77), 6), ((700, 611), 11)])
+def test_link_tiles_bitwise_equal_split(P, dtype, site, shape, steps):
+    print("tile2 links %s n=%d site=%s %s" % (shape, steps, site, dtype), flush=True)
+    nx, ny = shape
+    f0 = rand_state((ny, nx), 77, dtype)
+    g = np.random.default_rng(78)
+    V = [torch.from_numpy(g.standard_normal((ny, nx))) for _ in range(4)]
+    U = [torch.from_numpy(np.exp(1j * g.uniform(0, 6.28, (ny, nx)))).to(dtype) for _ in range(8)]
+    lats = []
+    for kernel in ("split", "auto"):
+        lat = P.Lattice2D(nx, ny, dtype=dtype, dt=workloads.DT2)
+        lat.set_kernel(kernel)
+        lat.set_fields(0.4, V) if site else lat.set_potential_z(0.4)
+        lat.set_links(U)
+        lat.load(f0)
+        lat.step(steps)
+        lats.append(lat)
+    s, a = lats
+    assert same(s.state(), a.state()) and a.current == steps % 2
+    assert torch.equal(s.step_norm(3), a.step_norm(3)) and same(s.state(), a.state())
+
+
 def test_shared_buffers_stay_in_place(P):
     """A zero-boundary context whose two buffer sets are one steps in place."""
     from paper_1309_3452_amd import _abi
