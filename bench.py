@@ -61,11 +61,14 @@ def parse():
     return ap.parse_args()
 
 
-def kernel_source_hash(steps_per_launch=1):
+def kernel_source_hash(steps_per_launch=1, march=False):
     """Hash of the kernel sources' code (comments and blank space removed), so
-    that a profile stays attached to the code it measured."""
+    that a profile stays attached to the code it measured. march: the register
+    z-march of complex128 lattices in place of the LDS marches."""
     h = hashlib.sha256()
-    for f in ("fused2.hip" if steps_per_launch == 2 else "fused.hip", "stencil3.h", "device.h", "internal.h"):
+    own = ("march3r.h", "march3r_c128.hip", "tile2.h") if march else \
+        ("fused2.hip" if steps_per_launch == 2 else "fused.hip",)
+    for f in own + ("stencil3.h", "device.h", "internal.h"):
         with open(os.path.join(ROOT, "paper_1309_3452_amd", "csrc", f)) as fh:
             text = fh.read()
         text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)
@@ -74,17 +77,18 @@ def kernel_source_hash(steps_per_launch=1):
     return h.hexdigest()[:16]
 
 
-def profiled_traffic(dtype_tag, n, steps_per_launch=1):
+def profiled_traffic(dtype_tag, n, steps_per_launch=1, march=False):
     """HBM bytes per launch from the committed rocprofv3 counter summary, if it
     was taken on the current kernel source; else None."""
-    name = "fused3d_%s_%d_counters.md" if steps_per_launch == 1 else "fused3dx2_%s_%d_counters.md"
+    name = "march3r_%s_%d_counters.md" if march else \
+        "fused3d_%s_%d_counters.md" if steps_per_launch == 1 else "fused3dx2_%s_%d_counters.md"
     path = os.path.join(ROOT, "profiles", name % (dtype_tag, n))
     if not os.path.exists(path):
         return None
     text = open(path).read()
     m = re.search(r"kernel_source_sha:\s*([0-9a-f]+)", text)
     t = re.search(r"hbm_bytes_per_launch:\s*([0-9.eE+]+)", text)
-    if not m or not t or m.group(1) != kernel_source_hash(steps_per_launch):
+    if not m or not t or m.group(1) != kernel_source_hash(steps_per_launch, march):
         return None
     return float(t.group(1))
 
@@ -383,9 +387,12 @@ def bench_batched(steps):
     best = min(res, key=res.get)
     value = cells * steps / (res[best] * 1e-3)
     alg = 96.0 * cells            # 4 complex64 amplitudes read + 4 written, 4 complex64 per-site records read, per cell-pass
-    # tuning candidates 8..14 of the batch library make two-step passes (mode 1 only;
-    # the persistent mode makes one-step passes); a two-step pass moves each byte once
-    spp = 2 if (best.startswith("mode1") and choice[0] >= 8) else 1
+    # tuning candidates 8..14 of the batch library make two-step passes and 15 the
+    # register-tile passes of up to 8 steps, bound by their arithmetic; a pass moves each
+    # byte once. A lattice may take shorter passes, so the rate below is a lower bound there
+    cand = choice[0] if best.startswith("mode1") else choice[1]
+    spp = 8 if cand == 15 else 2 if cand >= 8 else 1
+    passes = -(-steps // spp)
     return {"metric": "site-updates/s, 64 batched (2+1)D lattices, complex64, 500 steps", "value": value,
             "unit": "site-updates/s", "n_gpus": 1, "steps": steps, "warmup": 2,
             "ms_per_step": res[best] / steps, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
@@ -396,10 +403,11 @@ def bench_batched(steps):
             "variants_ms": res, "sequential_single_lattice_ms": solo_ms, "speedup_vs_sequential": solo_ms / res[best],
             # per pass (one launch) every amplitude is read and written once and every
             # record read once: 96 B per cell and pass, whatever the steps per pass
-            "roofline": {"bound": "hbm", "achieved": alg * steps / spp / (res[best] * 1e-3) / 1e9,
+            "roofline": {"bound": "valu" if spp == 8 else "hbm", "achieved": alg * passes / (res[best] * 1e-3) / 1e9,
                          "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                         "frac": alg * steps / spp / (res[best] * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                         "traffic": None, "alg_bytes_per_launch": alg, "steps_per_pass": spp,
+                         "frac": alg * passes / (res[best] * 1e-3) / 1e9 / HBM_PEAK_GBS,
+                         "traffic": None, "alg_bytes_per_launch": alg, "max_steps_per_pass": spp, "min_passes": passes,
+                         "achieved_is_lower_bound": spp == 8,
                          "effective_GBs_per_step_model": alg * steps / (res[best] * 1e-3) / 1e9}}
 
 
@@ -566,7 +574,7 @@ def bench_site3d(n, steps, dtype_name):
     torch.cuda.empty_cache()
     e0 = lat.norm()
     out = {}
-    for kern in ("fused", "fused2"):
+    for kern in ("fused", "fused2", "auto"):
         lat.set_kernel(kern)
         lat.step(2)
         out[kern] = _timed(lambda: lat.step(steps)) / steps
@@ -576,8 +584,8 @@ def bench_site3d(n, steps, dtype_name):
     # per cell-step: 16 amplitudes read or written once, 8 per-site records read
     # once (complex64 gamma or float64 theta, 8 B each)
     alg_step = (16 * b + 8 * 8) * cells
-    ms = out["fused2"]
-    # the two-step launch reads and writes each amplitude and reads each record
+    ms = out["auto"]
+    # the default's two-step launch reads and writes each amplitude and reads each record
     # once at least: alg_step bytes per launch (two steps)
     achieved = alg_step / (2 * ms * 1e-3) / 1e9
     return {"metric": "site-updates/s, (3+1)D %d^3 with per-site potential records" % n,
@@ -586,13 +594,14 @@ def bench_site3d(n, steps, dtype_name):
             "vs_baseline": None, "dtype": dtype_name, "data": "synthetic",
             "config": {"workload": "(3+1)D %d^3 lattice of the headline workload with V(x, y, z) = the z-step "
                                    "plus 0.05 N(0,1) per site as per-site coefficient records, m = 0.5, "
-                                   "two-step z-march kernel" % n, "cells": cells},
+                                   "default kernel (two steps per launch)" % n, "cells": cells},
             "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": achieved / HBM_PEAK_GBS, "traffic": None,
-                         "kernel": "k3_fused2 per-site (two steps per launch)", "avg_launch_ms": 2 * ms,
+                         "kernel": "k3_fused2 per-site" if dtype_name == "f32" else "k3_march3r per-site",
+                         "avg_launch_ms": 2 * ms,
                          "alg_bytes_per_launch": alg_step,
                          "effective_GBs_per_step_model": alg_step / (ms * 1e-3) / 1e9},
-            "one_step_kernel_ms_per_step": out["fused"],
+            "lds_march_ms_per_step": out["fused2"], "one_step_kernel_ms_per_step": out["fused"],
             "E_r_rel_drift": abs(e1[0] - e0[0]) / abs(e0[0])}
 
 
@@ -635,7 +644,7 @@ def bench_reverse3d(n, steps, dtype_name):
                                    "reversed A,B half-step" % (n, steps), "cells": cells},
             "roofline": {"bound": "hbm", "achieved": alg / (2 * rev * 1e-3) / 1e9, "peak": HBM_PEAK_GBS,
                          "unit": "GB/s", "frac": alg / (2 * rev * 1e-3) / 1e9 / HBM_PEAK_GBS, "traffic": None,
-                         "kernel": "k3_fused2 with the reversed tables", "alg_bytes_per_launch": alg},
+                         "kernel": ("k3_fused2" if dtype_name == "f32" else "k3_march3r") + " with the reversed tables", "alg_bytes_per_launch": alg},
             "forward_ms_per_step": fwd, "forward_one_step_kernel_ms_per_step": fwd1,
             "reverse_split_ms_per_step": rev_split, "reverse_over_forward": rev / fwd,
             "reverse_over_one_step_forward": rev / fwd1,
@@ -700,7 +709,10 @@ def bench_klein2d(phi_deg):
     variants["fused2_graph"] = _timed(lambda: graph.replay(), reps=3) / gsteps
     best = min(variants, key=variants.get)
     ms_step = variants[best]
-    spp = 1 if best == "fused" else 2        # steps per launch (auto is the two-step march at this size)
+    # auto: register tiles, up to 8 steps per pass, bound by their arithmetic (a lower bound of
+    # the byte rate: shorter passes move more); launches of the two timed segments together
+    spp = {"auto": 8, "fused": 1}.get(best, 2)
+    launches = sum(-(-n // spp) for n in seg) / steps        # per step
     alg = 96.0 * cells          # per launch: 4 complex64 amplitudes read + written, 4 complex64 coefficient records read
     return {"metric": "site-updates/s, (2+1)D Klein-step scattering %dx%d complex64" % (nx, ny),
             "value": cells / (ms_step * 1e-3), "unit": "site-updates/s", "n_gpus": 1, "steps": steps,
@@ -710,17 +722,19 @@ def bench_klein2d(phi_deg):
                                    "sigma=30 at %g deg from the step normal, absorbing frame of width 32, "
                                    "per-site complex coefficient records" % (nx, ny, phi_deg), "cells": cells},
             "variants_ms_per_step": variants, "best": best,
-            "roofline": {"bound": "hbm", "achieved": alg / (spp * ms_step * 1e-3) / 1e9, "peak": HBM_PEAK_GBS,
-                         "unit": "GB/s", "frac": alg / (spp * ms_step * 1e-3) / 1e9 / HBM_PEAK_GBS, "traffic": None,
-                         "alg_bytes_per_launch": alg, "steps_per_launch": spp,
+            "roofline": {"bound": "valu" if spp == 8 else "hbm", "achieved": alg * launches / (ms_step * 1e-3) / 1e9,
+                         "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                         "frac": alg * launches / (ms_step * 1e-3) / 1e9 / HBM_PEAK_GBS, "traffic": None,
+                         "alg_bytes_per_launch": alg, "max_steps_per_launch": spp,
+                         "achieved_is_lower_bound": spp == 8,
                          "effective_GBs_per_step_model": alg / (ms_step * 1e-3) / 1e9},
             "physics": {"transmitted_probability_t250": meas[0][0], "transmitted_probability_t350": meas[1][0],
                         "refraction_angle_deg": angle}}
 
 
 def bench_links2d(n, steps):
-    """(2+1)D n^2 complex64 lattice in a uniform magnetic field (Landau-gauge links),
-    the link y-march against the split link kernels."""
+    """(2+1)D n^2 complex64 lattice in a uniform magnetic field (Landau-gauge links):
+    the default (register tiles), the one-step link y-march and the split link kernels."""
     import torch
 
     import paper_1309_3452_amd as P
@@ -735,22 +749,30 @@ def bench_links2d(n, steps):
     lat.set_kernel("split")
     lat.step(2)
     split_ms = _timed(lambda: lat.step(steps)) / steps
+    lat.set_kernel("fused")
+    lat.step(2)
+    march_ms = _timed(lambda: lat.step(steps)) / steps
     lat.set_kernel("auto")
     lat.step(2)
     ms = _timed(lambda: lat.step(steps)) / steps
     e1 = lat.norm()
     cells = n * n
-    alg = (8 + 8) * 8.0 * cells      # 4 amplitudes read + 4 written, 8 link factors read, per cell-step
+    # 4 amplitudes read + 4 written, 8 link factors read, per cell and pass of up to 8 steps
+    # (bound by the arithmetic; a run may take shorter passes, so the rate is a lower bound)
+    alg = (8 + 8) * 8.0 * cells
+    passes = -(-steps // 8)
     return {"metric": "site-updates/s, (2+1)D %d^2 complex64 in a uniform magnetic field (gauge links)" % n,
             "value": cells / (ms * 1e-3), "unit": "site-updates/s", "n_gpus": 1, "steps": steps, "warmup": 2,
             "ms_per_step": ms, "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f32",
             "data": "synthetic",
             "config": {"workload": "(2+1)D %d^2, m=0.3, Landau-gauge links of one flux pair across the torus, "
-                                   "Gaussian packet, link y-march" % n, "cells": cells},
-            "roofline": {"bound": "hbm", "achieved": alg / (ms * 1e-3) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                         "frac": alg / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, "traffic": None,
-                         "kernel": "k2_fused_links (one launch per step)", "alg_bytes_per_step": alg},
-            "split_kernels_ms_per_step": split_ms, "E_r_rel_drift": abs(e1[0] - e0[0]) / abs(e0[0])}
+                                   "Gaussian packet, register tiles" % n, "cells": cells},
+            "roofline": {"bound": "valu", "achieved": alg * passes / (steps * ms * 1e-3) / 1e9, "peak": HBM_PEAK_GBS,
+                         "unit": "GB/s", "frac": alg * passes / (steps * ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
+                         "traffic": None, "kernel": "k2_tile_links (up to 8 steps per pass)",
+                         "alg_bytes_per_launch": alg, "min_passes": passes, "achieved_is_lower_bound": True,
+                         "effective_GBs_per_step_model": alg / (ms * 1e-3) / 1e9},
+            "one_step_march_ms_per_step": march_ms, "split_kernels_ms_per_step": split_ms, "E_r_rel_drift": abs(e1[0] - e0[0]) / abs(e0[0])}
 
 
 def bench_slab3d(steps):
@@ -815,7 +837,7 @@ def bench_slab3d(steps):
 
 def bench_plane2d(steps):
     """(2+1)D 128^2, complex128, 200 steps: launch-bound; plain launches vs one
-    captured graph, for the one-step march and the two-step march."""
+    captured graph, for the default (register tiles), the one-step and the two-step march."""
     import torch
 
     import paper_1309_3452_amd as P
@@ -840,14 +862,14 @@ def bench_plane2d(steps):
         torch.cuda.current_stream().wait_stream(s)
         return plain, _timed(lambda: g.replay(), reps=5)
 
-    variants = {k: measure(k) for k in ("fused", "fused2")}
+    variants = {k: measure(k) for k in ("auto", "fused", "fused2")}
     best = min(variants, key=lambda k: variants[k][1])
     plain, graph = variants[best]
     cells = 128 * 128
     return {"metric": "site-updates/s, (2+1)D 128^2 complex128, 200 steps", "value": cells * steps / (graph * 1e-3),
             "unit": "site-updates/s", "n_gpus": 1, "steps": steps, "warmup": 2, "ms_per_step": graph / steps,
             "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f64", "data": "synthetic",
-            "config": {"workload": "(2+1)D 128^2 Gaussian packet, m=0, V=0, y-march kernel", "cells": cells,
+            "config": {"workload": "(2+1)D 128^2 Gaussian packet, m=0, V=0, %s kernel" % best, "cells": cells,
                        "kernel": best},
             "plain_launches_ms": plain, "graph_replay_ms": graph,
             "plain_value": cells * steps / (plain * 1e-3),
@@ -911,11 +933,14 @@ def main():
     n, K, W = args.n, args.steps, args.warmup
     cells = n ** 3
     K64 = args.fp64_steps or K
+    # the default for a complex128 lattice with V(z) tables at this size is the register march
+    march64 = args.kernel == "auto"
+    k64 = "k3_march3r<double>" if march64 else "k3_fused2<double>" if args.kernel == "fused2" else "k3_fused<double>"
     if args.precision == "f64":
         r64 = run_gpu(n, torch.complex128, K64, W, 0, 0, args.kernel)
         l64 = r64["launch_ms"] * 1e-3
         v64 = cells * K64 / r64["wall_s"]
-        t64 = profiled_traffic("fp64", n, r64["steps_per_launch"])
+        t64 = profiled_traffic("fp64", n, r64["steps_per_launch"], march64)
         print(json.dumps({"metric": "site-updates/s, (3+1)D %d^3 complex128 step" % n, "value": v64,
                           "unit": "site-updates/s", "n_gpus": 1, "steps": K64, "warmup": W,
                           "ms_per_step": r64["wall_s"] * 1e3 / K64, "higher_is_better": True, "scaling": "weak",
@@ -923,9 +948,9 @@ def main():
                           "config": {"workload": "(3+1)D %d^3 headline physics, complex128" % n, "cells": cells},
                           "roofline": {"bound": "hbm", "achieved": 256.0 * cells / l64 / 1e9, "peak": HBM_PEAK_GBS,
                                        "unit": "GB/s", "frac": 256.0 * cells / l64 / 1e9 / HBM_PEAK_GBS,
-                                       "traffic": t64, "avg_launch_ms": r64["launch_ms"],
+                                       "traffic": t64, "kernel": k64, "avg_launch_ms": r64["launch_ms"],
                                        "alg_bytes_per_launch": 256.0 * cells,
-                                       "kernel_source_sha": kernel_source_hash(r64["steps_per_launch"])}}),
+                                       "kernel_source_sha": kernel_source_hash(r64["steps_per_launch"], march64)}}),
               flush=True)
         return
     r32 = run_gpu(n, torch.complex64, K, W, args.tile_y, args.zchunk, args.kernel, keep=True)
@@ -1019,13 +1044,14 @@ def main():
         G64 = r64["steps_per_launch"]
         l64 = r64["launch_ms"] * 1e-3
         a64 = 256.0 * cells / l64 / 1e9
-        t64 = profiled_traffic("fp64", n, G64)
+        t64 = profiled_traffic("fp64", n, G64, march64)
         line["fp64"] = {"value": v64, "unit": "site-updates/s", "ms_per_step": r64["wall_s"] * 1e3 / K64,
                         "roofline_frac": a64 / HBM_PEAK_GBS, "achieved_GBs": a64,
                         "alg_bytes_per_launch": 256.0 * cells, "avg_launch_ms": r64["launch_ms"],
                         "traffic": t64, "hbm_frac": (t64 / l64 / 1e9 / HBM_PEAK_GBS) if t64 else None,
                         "effective_GBs_per_step_model": 256.0 * cells * G64 / l64 / 1e9,
-                        "steps_per_launch": G64, "kernel_source_sha": kernel_source_hash(G64)}
+                        "steps_per_launch": G64, "kernel": k64,
+                        "kernel_source_sha": kernel_source_hash(G64, march64)}
         line["fp32_speedup_over_fp64"] = value / v64
         line["norm_error"]["E_r_rel_drift_fp64"] = acc64["E_r_rel_drift"] if acc64 else None
         line["norm_error"]["packet_vs_fp64"] = packet
