@@ -105,16 +105,31 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
     auto edge = [&](int buf, int l, int c, int wave) -> C & {
         return e[((((SB ? 0 : buf) * NL + l) * 2 + c) * NW + wave) * 64 + lane];
     };
-    // plane of half-plane h, as it is (kr) and wrapped (kw), advanced along the march;
-    // stored index of plane kr - d: wrapped, or offset by the slab's halo (what a
-    // level computes from planes outside the halo reaches no stored value: any
-    // stored plane serves), or, with zero values outside, any plane there
-    int kr = z0 - T, kw = wrapn(kr, nz);
+    // plane of half-plane h, as it is (kr) and among the stored ones (kw), advanced
+    // along the march; stored index of plane kr - d.  A slab's planes, and those of a
+    // lattice with zero values outside, end; what a level computes from planes beyond
+    // them reaches no stored value, so any stored plane serves there.
+    // Below 16 rows (EARLY) an iteration is one block without branches, which the
+    // compiler can schedule: planes wrap by selects, loads go out unconditionally (the
+    // last ones unused), and the tables' coefficients are read an iteration ahead, as
+    // scalar loads right before their use put four latencies into each iteration.  Two
+    // steps of 64^3: complex64 17.5 -> 15.4 us, with records 20.7 -> 17.4; complex128
+    // 22.7 -> 21.3, with records 28.0 -> 26.9, and 200 x 168 x 152 with records
+    // 442 -> 413.  With 16 waves the others hide the latencies and the registers it
+    // takes cost more (224 x 192 x 256, zero boundary: 290 -> 307 us), as do the masks
+    // a zero boundary needs then (128^3 complex128: 129 -> 132).
+    constexpr bool EARLY = K * NW < 16 && !ZB;
+    const int nzs = nz + 2 * zh;
+    int kr = z0 - T, kw = EARLY ? wrapn(kr + zh, nzs) : wrapn(kr, nz);
     int dm[T + 2];
 #pragma unroll
-    for (int d = 0; d < T + 2; ++d) dm[d] = d % nz;
+    for (int d = 0; d < T + 2; ++d) dm[d] = d % (EARLY ? nzs : nz);
     auto stored = [&](int d) __attribute__((always_inline)) -> int {
-        if (zh) return min(max(kr - d + zh, 0), nz + 2 * zh - 1);
+        if constexpr (EARLY) {
+            const int k = d < 0 ? kw + 1 - nzs : kw - dm[d < 0 ? 0 : d];
+            return k < 0 ? k + nzs : k;
+        }
+        if (zh) return min(max(kr - d + zh, 0), nzs - 1);
         if (d < 0) return kw + 1 == nz ? 0 : kw + 1;
         const int k = kw - dm[d < 0 ? 0 : d];
         return k < 0 ? k + nz : k;
@@ -192,6 +207,19 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
         return q;
     };
 
+    // the coefficients of this iteration, and those of the one after a phase PH
+    constexpr bool AHEAD = EARLY && SITE == 0;
+    Coef<R> kc[SITE ? 1 : NL];
+    auto tables = [&](auto PH, Coef<R>(&q)[SITE ? 1 : NL]) __attribute__((always_inline)) {
+        constexpr int ph = decltype(PH)::value;
+        if constexpr (AHEAD)
+#pragma unroll
+            for (int l = 1; l <= NL; ++l) {
+                const bool geven = ((ph + 1 + l) & 1) == 0;
+                q[l - 1] = tcoef((l & 1) ? (geven ? 0 : 1) : (geven ? 3 : 2), stored((ph & 1) ? (l + 1) / 2 - 1 : l / 2));
+            }
+    };
+
     // iteration hh, hh - hs = PH (mod 6); FILL: hh - hs = PH, where level l has
     // nothing yet that a stored value depends on before iteration 2 l
     auto iter = [&](auto PH, auto FILL, int hh) __attribute__((always_inline)) {
@@ -217,7 +245,7 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
         // iteration they cost 2 to 6% less time than in one burst (256^3 complex64
         // 271 against 281 us per step; with records 17% more, so there they stay).
         auto next = [&](int what) __attribute__((always_inline)) {
-            if (hh < he)
+            if (EARLY || hh < he)
                 load(std::integral_constant<bool, (ph & 1) == 1>(), std::integral_constant<int, (ph & 1) ? -1 : 0>(),
                      std::integral_constant<int, 0>(), std::integral_constant<int, (ph & 1) ? 0 : 1>(), what);
         };
@@ -246,7 +274,8 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
             const int g = hh - l;
             const C up = edge(br, l - 1, 0, wa), dn = edge(br, l - 1, 1, wb);
             Coef<R> kt{};
-            if constexpr (SITE == 0) kt = tcoef(first ? (geven ? 0 : 1) : (geven ? 3 : 2), stored(d));
+            if constexpr (AHEAD) kt = kc[SITE ? 0 : l - 1];
+            else if constexpr (SITE == 0) kt = tcoef(first ? (geven ? 0 : 1) : (geven ? 3 : 2), stored(d));
             const bool zin = inz(d);
             const bool st = l >= NL - 1 && g >= 2 * z0 && g < 2 * z1;
             const size_t po = (size_t)(uint32_t)(kr - d + zh) * pbytes;
@@ -335,21 +364,34 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
             put(std::integral_constant<int, 1>(), 0);
         }
         if constexpr (T > 1 && fill >= 3) level(std::integral_constant<int, (T > 1 ? 3 : 1)>());
+        Coef<R> kn[SITE ? 1 : NL];
+        tables(std::integral_constant<int, ph>(), kn);
         if constexpr (T > 1 && fill >= 4) level(std::integral_constant<int, (T > 1 ? 4 : 2)>());
         if constexpr (T > 2 && fill >= 5) level(std::integral_constant<int, (T > 2 ? 5 : 1)>());
         if constexpr (T > 2 && fill >= 6) level(std::integral_constant<int, (T > 2 ? 6 : 2)>());
         // the edges written, those of the previous iteration read: a barrier that
         // waits for this wave's LDS operations only (loads and stores stay in flight)
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if constexpr (AHEAD)
+#pragma unroll
+            for (int l = 0; l < NL; ++l) {
+                asm volatile("" : "+s"(kn[l].c1.x), "+s"(kn[l].c1.y), "+s"(kn[l].c2.x), "+s"(kn[l].c2.y));
+                kc[l] = kn[l];
+            }
         if constexpr (ph & 1) {
             ++kr;
-            kw = kw + 1 == nz ? 0 : kw + 1;
+            kw = kw + 1 == (EARLY ? nzs : nz) ? 0 : kw + 1;
         }
     };
 
     // for h = hs = 2k: D of plane k, B of k-1
     load(std::integral_constant<bool, true>(), std::integral_constant<int, 0>(), std::integral_constant<int, 1>(),
          std::integral_constant<int, 1>(), 3);
+    // phase -1's successor is iteration hs, one half-plane on
+    if constexpr (AHEAD)
+#pragma unroll
+        for (int l = 1; l <= NL; ++l)
+            kc[l - 1] = tcoef((l & 1) ? 1 : 3, stored((l + 1) / 2));
     // 2 (z1 - z0) + 4 T iterations: an even number, at least six
     constexpr std::true_type filling{};
     constexpr std::false_type full{};
@@ -414,12 +456,15 @@ struct M3Pick {
     double us = 0.0;
 };
 
-// Tile width: 56 cells keep every row's stores on whole 64-byte pieces (60 of
-// them measured 13% slower at 512^3, partial lines being written twice); the full
-// 64 - 2T where that saves one of at most five tile columns.
-inline int m3_width(int nx, int T) {
-    const int full = 64 - 2 * T, nf = (nx + full - 1) / full, n56 = (nx + 55) / 56;
-    return n56 <= 5 && nf < n56 ? full : 56;
+// Tile width: 56 complex64 cells keep every row's stores on whole 64-byte pieces (60
+// of them measured 13% slower at 512^3, partial lines being written twice); the full
+// 64 - 2T where that saves one of at most five tile columns.  60 complex128 cells are
+// whole pieces too and serve wherever they save a column (512^3: 7.15 against 7.62 ms
+// per two steps; with as many columns 56, whole lines, is ahead: 256^3 0.87 and 0.92).
+template <typename R> inline int m3_width(int nx, int T) {
+    const int full = sizeof(R) == 8 ? std::min(60, 64 - 2 * T) : 64 - 2 * T;
+    const int nf = (nx + full - 1) / full, n56 = (nx + 55) / 56;
+    return (sizeof(R) == 8 || n56 <= 5) && nf < n56 ? full : 56;
 }
 
 // The fastest of `count` shapes for T steps.  A chunk of p planes takes 2 p + 4 T
@@ -427,8 +472,9 @@ inline int m3_width(int nx, int T) {
 // about 2 (p + T).  Workgroups run in rounds of one or two per CU.  The last pick
 // for each (T, boundary) is kept per thread.  Periodic rows that divide 64
 // need no ring in x: built for the shapes of one row per thread and two steps, which
-// such lattices take (two steps of 64^3: complex64 17.1 against 21 us, complex128
-// 21.7 against 28, with records 28 against 39).
+// such lattices take (two steps of 64^3 with and without, when added: complex64 17.1
+// and 21 us, complex128 21.7 and 28, with records 28 and 39).
+template <typename R>
 static const M3Pick &m3_pick(const M3Shape *sh, int count, int T, bool zb, int nx, int ny, int nz) {
     struct Memo {
         int nx = -1, ny = -1, nz = -1;
@@ -444,7 +490,7 @@ static const M3Pick &m3_pick(const M3Shape *sh, int count, int T, bool zb, int n
         M3Pick p;
         p.shape = q;
         p.xp = !zb && T == 2 && sh[q].K == 1 && 64 % nx == 0;
-        p.tw = p.xp ? nx : m3_width(nx, T);
+        p.tw = p.xp ? nx : m3_width<R>(nx, T);
         p.nty = (ny + sh[q].K * sh[q].NW - 2 * T - 1) / (sh[q].K * sh[q].NW - 2 * T);
         const int64_t tiles = (int64_t)((nx + p.tw - 1) / p.tw) * p.nty;
         for (int occ = 1; occ <= sh[q].occ; ++occ) {

@@ -9,7 +9,7 @@ namespace {
 constexpr M3Shape kShapes[] = {{1, 2, 8, 1, 5.6}, {2, 1, 8, 1, 2.15}};
 
 const M3Pick &pick(int steps, bool zb, int nx, int ny, int nz) {
-    return m3_pick(kShapes, sizeof(kShapes) / sizeof(kShapes[0]), steps, zb, nx, ny, nz);
+    return m3_pick<double>(kShapes, sizeof(kShapes) / sizeof(kShapes[0]), steps, zb, nx, ny, nz);
 }
 }  // namespace
 

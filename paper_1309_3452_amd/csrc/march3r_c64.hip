@@ -10,7 +10,7 @@ constexpr M3Shape kShapes[] = {{1, 4, 8, 1, 5.0}, {2, 2, 16, 1, 4.6}, {2, 1, 16,
                                {3, 3, 8, 1, 5.8}, {3, 1, 12, 1, 2.05}};
 
 const M3Pick &pick(int steps, bool zb, int nx, int ny, int nz) {
-    return m3_pick(kShapes, sizeof(kShapes) / sizeof(kShapes[0]), steps, zb, nx, ny, nz);
+    return m3_pick<float>(kShapes, sizeof(kShapes) / sizeof(kShapes[0]), steps, zb, nx, ny, nz);
 }
 }  // namespace
 

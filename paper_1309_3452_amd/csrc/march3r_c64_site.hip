@@ -8,7 +8,7 @@ namespace {
 constexpr M3Shape kShapes[] = {{1, 2, 8, 1, 3.6}, {2, 2, 8, 1, 3.3}, {2, 1, 8, 1, 1.25}};
 
 const M3Pick &pick(int steps, bool zb, int nx, int ny, int nz) {
-    return m3_pick(kShapes, sizeof(kShapes) / sizeof(kShapes[0]), steps, zb, nx, ny, nz);
+    return m3_pick<float>(kShapes, sizeof(kShapes) / sizeof(kShapes[0]), steps, zb, nx, ny, nz);
 }
 }  // namespace
 

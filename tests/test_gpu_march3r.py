@@ -92,3 +92,38 @@ def test_shared_buffers_stay_in_place(P):
         lat.reverse(3)
         lats.append(lat)
     assert lats[1].current == 0 and same(lats[0].state(), lats[1].state())
+
+
+@pytest.mark.parametrize("nx,ny,nz", [(340, 5, 4), (421, 9, 7)])
+def test_wide_rows_of_60_columns(P, nx, ny, nz):
+    """complex128 rows that 60-column tiles cover with fewer columns than 56-column ones."""
+    print("march3r wide %dx%dx%d" % (nx, ny, nz), flush=True)
+    g = np.random.default_rng(83)
+    f0 = [torch.from_numpy(g.standard_normal((nz, ny, nx)) + 1j * g.standard_normal((nz, ny, nx))) for _ in range(8)]
+    lats = []
+    for kernel in ("split", "auto"):
+        lat = P.Lattice3D(nx, ny, nz, dtype=torch.complex128, dt=workloads.DT3)
+        lat.set_kernel(kernel)
+        lat.set_potential_z(0.4, np.full(nz, 0.3), np.linspace(0.1, 0.9, nz))
+        lat.load(f0)
+        lat.step(5)
+        lats.append(lat)
+    assert same(lats[0].state(), lats[1].state())
+
+
+@pytest.mark.parametrize("slabs", [1, 2, 5])
+def test_slab_planes_wrap(P, slabs):
+    """Slabs of few planes (2 to 10) under the march, whose plane index wraps over the stored planes."""
+    print("march3r slabs %d" % slabs, flush=True)
+    g = np.random.default_rng(84)
+    nx, ny, nz = 61, 14, 10
+    f0 = [torch.from_numpy(g.standard_normal((nz, ny, nx)) + 1j * g.standard_normal((nz, ny, nx))) for _ in range(8)]
+    vi, vh = g.standard_normal(nz), g.standard_normal(nz)
+    whole = P.Lattice3D(nx, ny, nz, dtype=torch.complex128, dt=workloads.DT3)
+    parts = P.SlabDecomposition(nx, ny, nz, slabs, dtype=torch.complex128, dt=workloads.DT3)
+    whole.set_kernel("split")
+    for lat in (whole, parts):
+        lat.set_potential_z(0.4, vi, vh)
+        lat.load(f0)
+        lat.step(6)
+    assert same(whole.state(), parts.state())
