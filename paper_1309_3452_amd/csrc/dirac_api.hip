@@ -241,10 +241,10 @@ bool tile2_applies(const dirac_ctx *c) {
 // (3+1)D likewise: the register march (march3r.h) where it is the fastest kernel.
 // Per launch of two steps, next to the LDS march (one-step one for an odd
 // complex64 width, split kernels with zero values outside): complex128 256^3
-// 0.88 against 0.99 ms, 64^3 29 against 37 us, with records 200 x 168 x 152 0.45
-// against 0.69 ms; complex64 191 x 151 x 127 0.13 against 0.30, zero values outside
-// 224 x 192 x 256 0.35 against 0.96.  For complex64 of even width the two are
-// close and the tiles' fit decides (tables: 32^3 10 against 21 us, 64^3 22 / 26,
+// 0.87 against 0.99 ms, 64^3 21 against 37 us, with records 200 x 168 x 152 0.41
+// against 0.69 ms; complex64 191 x 151 x 127 0.14 against 0.30, zero values outside
+// 224 x 192 x 256 0.29 against 0.96.  For complex64 of even width the two are
+// close and the tiles' fit decides (tables: 32^3 9 against 21 us, 64^3 15 / 26,
 // 96^3 34 / 50, 128^3 88 / 79, 160^3 129 / 142, 256^3 545 / 447; records: 96^3 50 /
 // 79, 128^3 125 / 111, 200 x 168 x 152 251 / 342, 256^3 789 / 756): the estimates of
 // both, the register march's less 5%.

@@ -5,7 +5,7 @@ namespace dirac {
 
 namespace {
 // 16 rows by 8 waves of up to 256 registers (LDS edges take 128 KB), 8 rows, or 12
-// (64^3, two steps: 28.3 against 30.5 us with 8 rows).
+// (two steps of 200 x 168 x 152: 16 rows 0.29 ms, 8 rows 0.33, 12 rows 0.255).
 constexpr M3Shape kShapes[] = {{1, 2, 8, 1, 4.8}, {2, 2, 8, 1, 3.5}, {2, 1, 8, 1, 1.4}, {2, 1, 12, 1, 2.15}};
 
 const M3Pick &pick(int steps, bool zb, int nx, int ny, int nz) {
