@@ -109,16 +109,16 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
     // along the march; stored index of plane kr - d.  A slab's planes, and those of a
     // lattice with zero values outside, end; what a level computes from planes beyond
     // them reaches no stored value, so any stored plane serves there.
-    // Below 16 rows (EARLY) an iteration is one block without branches, which the
+    // Up to 16 rows (EARLY) an iteration is one block without branches, which the
     // compiler can schedule: planes wrap by selects, loads go out unconditionally (the
     // last ones unused), and the tables' coefficients are read an iteration ahead, as
     // scalar loads right before their use put four latencies into each iteration.  Two
-    // steps of 64^3: complex64 17.5 -> 15.4 us, with records 20.7 -> 17.4; complex128
+    // steps of 64^3: complex64 17.5 -> 15.3 us, with records 20.7 -> 17.4; complex128
     // 22.7 -> 21.3, with records 28.0 -> 26.9, and 200 x 168 x 152 with records
-    // 442 -> 413.  With 16 waves the others hide the latencies and the registers it
-    // takes cost more (224 x 192 x 256, zero boundary: 290 -> 307 us), as do the masks
-    // a zero boundary needs then (128^3 complex128: 129 -> 132).
-    constexpr bool EARLY = K * NW < 16 && !ZB;
+    // 442 -> 413.  With 16 rows the levels are kept apart (moved into each other they
+    // cost 191 x 151 x 127 139 us; apart 131, with the branches 135).  The masks that a
+    // zero boundary needs then cost more than it gains (128^3 complex128: 129 -> 132).
+    constexpr bool EARLY = K * NW <= 16 && !ZB, APART = EARLY && K * NW == 16;
     const int nzs = nz + 2 * zh;
     int kr = z0 - T, kw = EARLY ? wrapn(kr + zh, nzs) : wrapn(kr, nz);
     int dm[T + 2];
@@ -272,6 +272,7 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
             constexpr int sp = (ph + 18 - l + 1) % 3, sm = (ph + 18 - l) % 3, so = (ph + 18 - l - 1) % 3;
             constexpr int d = (l - (ph & 1) + 1) / 2;                // plane of g: kr - d
             const int g = hh - l;
+            if constexpr (APART) __builtin_amdgcn_sched_barrier(0);
             const C up = edge(br, l - 1, 0, wa), dn = edge(br, l - 1, 1, wb);
             Coef<R> kt{};
             if constexpr (AHEAD) kt = kc[SITE ? 0 : l - 1];
