@@ -410,8 +410,10 @@ int dirac_adjoint_vz(dirac_ctx *ctx, int64_t n, void *const lam[], void *dLdV_in
                      void *stream);
 
 /* dirac_adjoint_vz with a second set of arrays for lam: work[] are 8 caller-owned
- * device arrays shaped like lam, their contents lost, none of them a lam or state
- * array (DIRAC_E_ARG), or work is NULL (dirac_adjoint_vz itself).  With them, on
+ * device arrays shaped like lam, their contents lost, or NULL (dirac_adjoint_vz
+ * itself).  No work array may overlap another, a lam or a state array, and with work
+ * no lam array a state array of either set, the idle one included (DIRAC_E_ARG).
+ * With them, on
  * lattices large enough to gain, a backward step is one launch that ping-pongs the
  * state between its two buffer sets and lam between lam[] and work[]; on return both are where
  * dirac_adjoint_vz leaves them, with the same bits (the gradient: the same FP64

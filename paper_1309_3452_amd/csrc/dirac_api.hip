@@ -992,11 +992,22 @@ int dirac_adjoint_vz_work(dirac_ctx *c, int64_t n, void *const lam[], void *cons
     if (n < 0 || !lam || !dLdV_int || !dLdV_half) return fail(c, DIRAC_E_ARG, "bad arguments");
     for (int q = 0; q < 8; ++q)
         if (!lam[q]) return fail(c, DIRAC_E_ARG, "null lam array %d", q);
+    // the march reads and writes lam, work and both buffer sets at once: no two of
+    // their arrays may share memory
+    const size_t bytes = (size_t)c->nx * (size_t)c->ny * (size_t)c->nz * (c->dtype == DIRAC_C64 ? 8u : 16u);
+    auto meet = [bytes](const void *a, const void *b) {
+        const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+        return x < y + bytes && y < x + bytes;
+    };
     for (int q = 0; work && q < 8; ++q) {
         if (!work[q]) return fail(c, DIRAC_E_ARG, "null work array %d", q);
-        for (int p = 0; p < 8; ++p)
-            if (work[q] == lam[p] || work[q] == c->buf[0][p] || work[q] == c->buf[1][p])
-                return fail(c, DIRAC_E_ARG, "work array %d is a state or lam array", q);
+        for (int p = 0; p < 8; ++p) {
+            if (meet(work[q], lam[p]) || meet(work[q], c->buf[0][p]) || meet(work[q], c->buf[1][p]) ||
+                (p < q && meet(work[q], work[p])))
+                return fail(c, DIRAC_E_ARG, "work array %d overlaps a state, lam or work array", q);
+            if (meet(lam[q], c->buf[0][p]) || meet(lam[q], c->buf[1][p]))
+                return fail(c, DIRAC_E_ARG, "lam array %d overlaps a state array", q);
+        }
     }
     const uint64_t plane_bytes = (uint64_t)c->nx * (uint64_t)c->ny * (c->dtype == DIRAC_C64 ? 8u : 16u);
     const bool march = work && plane_bytes < (1ull << 32) && !sets_shared(c) &&
