@@ -53,6 +53,16 @@ size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 // mode, the halo planes on both sides.
 int64_t planes_of(const dirac_ctx *c) { return c->nz + 2 * c->zh; }
 
+size_t array_bytes(const dirac_ctx *c) {
+    return (size_t)c->nx * (size_t)c->ny * (size_t)planes_of(c) * (c->dtype == DIRAC_C64 ? 8u : 16u);
+}
+
+// Two arrays of that many bytes overlap.
+bool ranges_meet(const void *a, const void *b, size_t bytes) {
+    const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+    return x < y + bytes && y < x + bytes;
+}
+
 // theta of class q (A, B, C, D) at plane k: (dt/2)(+-m + V at the class's z).
 double theta_of(const dirac_ctx *c, int q, int64_t k) {
     double h = 0.5 * c->dt;
@@ -223,12 +233,13 @@ int64_t flips_of(const dirac_ctx *c, int64_t n) {
     return kc == DIRAC_KERNEL_SPLIT ? 0 : kc == DIRAC_KERNEL_FUSED2 ? n / 2 + (n & 1) : n;
 }
 
-// The two buffer sets share an array: only the in-place kernels can take that.
+// The two buffer sets share memory: only the in-place kernels can take that.
 bool sets_shared(const dirac_ctx *c) {
     const int narr = c->ndim == 3 ? 8 : 4;
+    const size_t bytes = array_bytes(c);
     for (int q = 0; q < narr; ++q)
         for (int p = 0; p < narr; ++p)
-            if (c->buf[0][q] == c->buf[1][p]) return true;
+            if (ranges_meet(c->buf[0][q], c->buf[1][p], bytes)) return true;
     return false;
 }
 
@@ -994,11 +1005,8 @@ int dirac_adjoint_vz_work(dirac_ctx *c, int64_t n, void *const lam[], void *cons
         if (!lam[q]) return fail(c, DIRAC_E_ARG, "null lam array %d", q);
     // the march reads and writes lam, work and both buffer sets at once: no two of
     // their arrays may share memory
-    const size_t bytes = (size_t)c->nx * (size_t)c->ny * (size_t)c->nz * (c->dtype == DIRAC_C64 ? 8u : 16u);
-    auto meet = [bytes](const void *a, const void *b) {
-        const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
-        return x < y + bytes && y < x + bytes;
-    };
+    const size_t bytes = array_bytes(c);
+    auto meet = [bytes](const void *a, const void *b) { return ranges_meet(a, b, bytes); };
     for (int q = 0; work && q < 8; ++q) {
         if (!work[q]) return fail(c, DIRAC_E_ARG, "null work array %d", q);
         for (int p = 0; p < 8; ++p) {
