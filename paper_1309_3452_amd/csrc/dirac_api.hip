@@ -249,6 +249,13 @@ bool tile2_applies(const dirac_ctx *c) {
     return c->ndim == 2 && c->kernel == DIRAC_KERNEL_AUTO && c->zchunk == 0 && !sets_shared(c);
 }
 
+// The register marches address a plane, and a V(z) table of four classes, with
+// 32-bit byte offsets (a complex128 table reaches 4 GiB at 2^25 planes).
+bool offsets_fit(const dirac_ctx *c) {
+    const uint64_t plane = (uint64_t)c->nx * (uint64_t)c->ny * (c->dtype == DIRAC_C64 ? 8u : 16u);
+    return plane < (1ull << 32) && (c->site_mode || tab_bytes_of(c) < (1ull << 32));
+}
+
 // (3+1)D likewise: the register march (march3r.h) where it is the fastest kernel.
 // Per launch of two steps, next to the LDS march (one-step one for an odd
 // complex64 width, split kernels with zero values outside): complex128 256^3
@@ -262,8 +269,7 @@ bool tile2_applies(const dirac_ctx *c) {
 bool march3_applies(const dirac_ctx *c) {
     if (c->ndim != 3 || c->kernel != DIRAC_KERNEL_AUTO || c->tile_y != 0 || c->zchunk != 0 || c->links_on || c->zh)
         return false;
-    const uint64_t plane_bytes = (uint64_t)c->nx * (uint64_t)c->ny * (c->dtype == DIRAC_C64 ? 8u : 16u);
-    if (plane_bytes >= (1ull << 32)) return false;
+    if (!offsets_fit(c)) return false;
     if (!c->zbc && c->dtype == DIRAC_C64 && c->nx % 2 == 0) {
         const int nx = (int)c->nx, ny = (int)c->ny, nz = (int)c->nz;
         if (march3r_us<float>(2, c->site_mode, false, nx, ny, nz) > 0.95 * march_lds_us(c->site_mode, nx, ny, nz)) return false;
@@ -1017,8 +1023,7 @@ int dirac_adjoint_vz_work(dirac_ctx *c, int64_t n, void *const lam[], void *cons
                 return fail(c, DIRAC_E_ARG, "lam array %d overlaps a state array", q);
         }
     }
-    const uint64_t plane_bytes = (uint64_t)c->nx * (uint64_t)c->ny * (c->dtype == DIRAC_C64 ? 8u : 16u);
-    const bool march = work && plane_bytes < (1ull << 32) && !sets_shared(c) &&
+    const bool march = work && offsets_fit(c) && !sets_shared(c) &&
                        adj_march_wins(c->dtype == DIRAC_C64, (int)c->nx, (int)c->ny, (int)c->nz);
     hipStream_t s = (hipStream_t)stream;
     rc = upload_tables(c, s);
