@@ -308,6 +308,20 @@ int dirac_coef_from_fields(void *coef, int dtype, double dt, double sgn_m, const
 int dirac_set_kernel(dirac_ctx *ctx, int kernel, int tile_y, int zchunk);
 
 /*
+ * Which kernels a call of n steps launches, in order, as text: "<count> x <kernel>
+ * <its shape>" joined by "; ", e.g. "3 x march3r steps=2 rows=1 waves=12 width=56
+ * chunks=5; 1 x fused".  split: two half-step launches in place; half: one of them;
+ * fused, fused2: one or two steps in a march through LDS; tile2: 2D register tiles;
+ * march3r: 3D register march (rows per thread, waves).  A functional that takes a
+ * launch of its own is not listed.  For tests and timing tools; the words may
+ * change.  Makes no launch.  DIRAC_E_ARG for a null argument, n < 0 (step_norm: n <
+ * 1) or another call; DIRAC_E_SHAPE where the text does not fit; DIRAC_E_STATE for a
+ * batch context.
+ */
+enum dirac_call { DIRAC_CALL_STEP = 0, DIRAC_CALL_REVERSE = 1, DIRAC_CALL_STEP_NORM = 2 };
+int dirac_route(dirac_ctx *ctx, int64_t n, int call, char *out, size_t len);
+
+/*
  * Advance the bound state by n >= 0 full steps (Sect. 2: A,B from n-1/2 to
  * n+1/2 by Eqs. ss1, ss2, then C,D from n to n+1 by Eqs. ss3, ss4; Sect. 3:
  * u then v by Eqs. scheme2Deq-scheme4thline).  Asynchronous on stream.

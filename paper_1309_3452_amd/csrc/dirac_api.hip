@@ -330,6 +330,50 @@ template <typename R> bool plan_march3(const dirac_ctx *c, int64_t n, int64_t fl
     return found;
 }
 
+// What a call launches, decided here for the call itself and for dirac_route.
+enum class Op { step, reverse, step_norm };
+enum class Way { split, fused, fused2, tile2, march3 };
+struct Route {
+    Way way = Way::split;
+    int64_t passes = 0;      // tile2
+    March3Plan plan;         // march3; of reversed steps those between the two half-steps
+};
+
+Way way_of(int kc) {
+    return kc == DIRAC_KERNEL_FUSED2 ? Way::fused2 : kc == DIRAC_KERNEL_FUSED ? Way::fused : Way::split;
+}
+
+template <typename R> Route route_of(const dirac_ctx *c, int64_t n, Op op) {
+    Route r;
+    const int kc = kernel_choice(c);
+    // the buffer sets end up as kernel_choice's kernel would leave them; step_norm by
+    // it makes its last launch (two steps or one) apart
+    const int64_t flips = op == Op::reverse || n == 0 ? 0
+                          : op == Op::step            ? flips_of(c, n)
+                          : c->ndim == 3 && kc == DIRAC_KERNEL_FUSED2 && n >= 2 ? flips_of(c, n - 2) + 1
+                                                                                : flips_of(c, n - 1) + flips_of(c, 1);
+    if (tile2_applies(c) && !(op == Op::reverse && c->links_on)) {
+        r.passes = tile2_passes(n, (int)(flips & 1), 1, &c->nx, &c->ny, sizeof(R) == 4,
+                                tile2_kind(c->site_mode, c->links_on));
+        if (r.passes > 0) {
+            r.way = Way::tile2;
+            return r;
+        }
+    }
+    if (op == Op::reverse) {
+        const bool march = march3_applies(c);
+        // 3D lattices whose forward steps take a march kernel reverse on it too
+        const bool old_march = c->ndim == 3 && !c->links_on && !c->zh && kc != DIRAC_KERNEL_SPLIT;
+        if ((old_march || n > 2) && march && (n == 1 || plan_march3<R>(c, n - 1, flips_of(c, n - 1), false, &r.plan)))
+            r.way = Way::march3;
+        else
+            r.way = old_march ? way_of(kc) : Way::split;
+        return r;
+    }
+    r.way = march3_applies(c) && plan_march3<R>(c, n, flips, op == Op::step_norm, &r.plan) ? Way::march3 : way_of(kc);
+    return r;
+}
+
 // The forward march kernels run the reversed sequence: with r -> -r, the
 // reversed coefficient tables (theta -> -theta) and per-site records read with
 // theta -> -theta they apply H1' then H2', the two half-steps solved backwards
@@ -346,12 +390,9 @@ template <typename R> FusedArgs<R> fused_args_rev(dirac_ctx *c) {
     return a;
 }
 
-// 3D lattices whose forward steps take a march kernel reverse on it too
-bool reverse_on_march(const dirac_ctx *c) {
-    if (c->ndim != 3 || c->links_on || c->zh) return false;
-    const int kc = kernel_choice(c);
-    return kc == DIRAC_KERNEL_FUSED || kc == DIRAC_KERNEL_FUSED2;
-}
+// A plan's one-step launches take the LDS march's one-step kernel where its rows are
+// whole (257^3 complex128: 0.84 against 0.97 ms).
+bool ones_on_fused(const dirac_ctx *c) { return !c->zbc && (c->dtype == DIRAC_C128 || c->nx % 2 == 0); }
 
 // The launches of a plan, forward or of the reversed sequence; with npart the
 // last one sums the functional and *nblocks receives its workgroups.
@@ -365,9 +406,7 @@ int run_march3(dirac_ctx *c, const March3Plan &plan, bool rev, hipStream_t s, do
             a.npart_cap = npart_cap;
         }
         const int steps = t < plan.threes ? 3 : t < plan.threes + plan.twos ? 2 : 1;
-        // one step: the LDS march's one-step kernel where its rows are whole (257^3
-        // complex128: 0.84 against 0.97 ms)
-        if (steps == 1 && !c->zbc && (sizeof(R) == 8 || c->nx % 2 == 0))
+        if (steps == 1 && ones_on_fused(c))
             HIPCHK(c, launch_fused3<R>(a, c->site_mode, 0, s, nblocks));
         else
             HIPCHK(c, launch_march3r<R>(a, steps, c->site_mode, c->zbc, s, nblocks));
@@ -376,20 +415,18 @@ int run_march3(dirac_ctx *c, const March3Plan &plan, bool rev, hipStream_t s, do
     return DIRAC_OK;
 }
 
-template <typename R> int run_reverse_march(dirac_ctx *c, int64_t n, hipStream_t s) {
+template <typename R> int run_reverse_march(dirac_ctx *c, int64_t n, const Route &r, hipStream_t s) {
     if (n <= 0) return DIRAC_OK;
     const bool site = c->site_mode;
-    March3Plan plan;
-    if (march3_applies(c) && (n == 1 || plan_march3<R>(c, n - 1, flips_of(c, n - 1), false, &plan))) {
-        HIPCHK(c, launch_half3<R>(half_args<R>(c, true), 1, site, s));      // H2'
-        const int rc = run_march3<R>(c, plan, true, s, nullptr, 0, nullptr);
+    HIPCHK(c, launch_half3<R>(half_args<R>(c, true), 1, site, s));      // H2'
+    if (r.way == Way::march3) {
+        const int rc = run_march3<R>(c, r.plan, true, s, nullptr, 0, nullptr);
         if (rc) return rc;
-        HIPCHK(c, launch_half3<R>(half_args<R>(c, true), 0, site, s));      // H1'
+        HIPCHK(c, launch_half3<R>(half_args<R>(c, true), 0, site, s));  // H1'
         return DIRAC_OK;
     }
-    HIPCHK(c, launch_half3<R>(half_args<R>(c, true), 1, site, s));      // H2'
     int64_t t = 1;
-    if (kernel_choice(c) == DIRAC_KERNEL_FUSED2) {
+    if (r.way == Way::fused2) {
         for (; t + 2 <= n; t += 2) {
             HIPCHK(c, launch_fused3x2<R>(fused_args_rev<R>(c), site, s));
             c->cur = 1 - c->cur;
@@ -403,12 +440,8 @@ template <typename R> int run_reverse_march(dirac_ctx *c, int64_t n, hipStream_t
     return DIRAC_OK;
 }
 
-// n steps on register tiles with `flips` mod 2 buffer-set flips; *done false
-// where there is no such split of n (then nothing was launched).
-template <typename R> int run_tile2(dirac_ctx *c, int64_t n, bool reverse, int64_t flips, hipStream_t s, bool *done) {
-    const int64_t passes = tile2_passes(n, (int)(flips & 1), 1, &c->nx, &c->ny, sizeof(R) == 4,
-                                        tile2_kind(c->site_mode, c->links_on));
-    *done = passes > 0;
+// n steps on register tiles in that many passes.
+template <typename R> int run_tile2(dirac_ctx *c, int64_t n, bool reverse, int64_t passes, hipStream_t s) {
     for (int64_t p = 0; p < passes; ++p) {
         const FusedArgs<R> a = reverse ? fused_args_rev<R>(c) : fused_args<R>(c);
         const int steps = (int)(n / passes + (p < n % passes));
@@ -422,8 +455,11 @@ template <typename R> int run_tile2(dirac_ctx *c, int64_t n, bool reverse, int64
 // Two steps of a (3+1)D lattice or z-slab in one launch: in complex128 a slab takes
 // the register march too, whose two-step reach is the slab's two halo planes
 // (512 x 512 x 64: 0.90 against 1.08 ms, with records 1.45 against 1.91).
+template <typename R> bool two_on_march3(const dirac_ctx *c) {
+    return sizeof(R) == 8 && c->ndim == 3 && c->zh && c->kernel == DIRAC_KERNEL_AUTO && c->zchunk == 0;
+}
 template <typename R> hipError_t launch_two(const dirac_ctx *c, const FusedArgs<R> &a, hipStream_t s, int *nblocks) {
-    if (sizeof(R) == 8 && c->zh && c->kernel == DIRAC_KERNEL_AUTO && c->zchunk == 0)
+    if (two_on_march3<R>(c))
         return launch_march3r<R>(a, 2, c->site_mode, false, s, nblocks);
     return launch_fused3x2<R>(a, c->site_mode, s, nblocks);
 }
@@ -431,20 +467,14 @@ template <typename R> hipError_t launch_two(const dirac_ctx *c, const FusedArgs<
 template <typename R> int run_steps(dirac_ctx *c, int64_t n, bool reverse, hipStream_t s) {
     int rc = upload_tables(c, s);
     if (rc) return rc;
-    if (tile2_applies(c) && !(reverse && c->links_on)) {
-        bool done = false;
-        rc = run_tile2<R>(c, n, reverse, reverse ? 0 : flips_of(c, n), s, &done);
-        if (rc || done) return rc;
-    }
-    if (reverse && (reverse_on_march(c) || (march3_applies(c) && n > 2))) return run_reverse_march<R>(c, n, s);
-    March3Plan plan;
-    if (!reverse && march3_applies(c) && plan_march3<R>(c, n, flips_of(c, n), false, &plan))
-        return run_march3<R>(c, plan, false, s, nullptr, 0, nullptr);
+    const Route r = route_of<R>(c, n, reverse ? Op::reverse : Op::step);
+    if (r.way == Way::tile2) return run_tile2<R>(c, n, reverse, r.passes, s);
+    if (reverse && r.way != Way::split) return run_reverse_march<R>(c, n, r, s);
+    if (r.way == Way::march3) return run_march3<R>(c, r.plan, false, s, nullptr, 0, nullptr);
     const bool site = c->site_mode;
-    const int kc = reverse ? DIRAC_KERNEL_SPLIT : kernel_choice(c);
-    const bool fused = kc == DIRAC_KERNEL_FUSED || kc == DIRAC_KERNEL_FUSED2;
+    const bool fused = r.way != Way::split;
     int64_t t = 0;
-    if (kc == DIRAC_KERNEL_FUSED2) {
+    if (r.way == Way::fused2) {
         for (; t + 2 <= n; t += 2) {
             FusedArgs<R> a = fused_args<R>(c);
             if (c->ndim == 3) HIPCHK(c, launch_two<R>(c, a, s, nullptr));
@@ -480,6 +510,51 @@ template <typename R> int run_steps(dirac_ctx *c, int64_t n, bool reverse, hipSt
         }
     }
     return DIRAC_OK;
+}
+
+// The launches of a route in their order: name, count and what tells their shape.
+template <typename R> std::string route_text(const dirac_ctx *c, int64_t n, Op op) {
+    const Route r = route_of<R>(c, n, op);
+    const bool fp32 = sizeof(R) == 4;
+    std::string t;
+    auto add = [&t](int64_t count, const char *fmt, auto... v) {
+        if (count < 1) return;
+        char b[160];
+        snprintf(b, sizeof b, fmt, v...);
+        t += (t.empty() ? "" : "; ") + std::to_string((long long)count) + " x " + b;
+    };
+    const bool halves = op == Op::reverse && r.way != Way::split && r.way != Way::tile2 && n > 0;
+    int64_t m = halves ? n - 1 : n;
+    if (halves) add(1, "%s", "half");
+    if (r.way == Way::tile2) {
+        const int kind = tile2_kind(c->site_mode, c->links_on);
+        for (const int64_t more : {(int64_t)1, (int64_t)0}) {
+            const int steps = (int)(n / r.passes + more);
+            double us = 0.0;
+            const int64_t count = more ? n % r.passes : r.passes - n % r.passes;
+            if (count)
+                add(count, "tile2%s steps=%d rows=%d", c->links_on ? " links" : "", steps,
+                    tile2_rows(tile2_best_shape(steps, 1, &c->nx, &c->ny, fp32, kind, &us)));
+        }
+    } else if (r.way == Way::march3) {
+        const int64_t counts[4] = {0, r.plan.ones, r.plan.twos, r.plan.threes};
+        for (int T = 3; T > 0; --T) {
+            if (counts[T] == 0) continue;
+            if (T == 1 && ones_on_fused(c)) {
+                add(counts[T], "%s", "fused");
+                continue;
+            }
+            const M3Pick &p = march3r_pick<R>(T, c->site_mode, c->zbc, (int)c->nx, (int)c->ny, (int)c->nz);
+            add(counts[T], "march3r steps=%d rows=%d waves=%d width=%d chunks=%d%s", T, p.K, p.NW, p.tw, p.nzc,
+                p.xp ? " rotating" : "");
+        }
+    } else {
+        if (r.way == Way::fused2) add(m / 2, "%s", two_on_march3<R>(c) ? "march3r steps=2" : "fused2");
+        if (r.way == Way::fused2) m &= 1;
+        add(m, "%s", r.way == Way::split ? "split" : c->links_on ? "fused links" : "fused");
+    }
+    if (halves) add(1, "%s", "half");
+    return t;
 }
 
 template <typename R> ReduceArgs<R> reduce_args(dirac_ctx *c, double z0) {
@@ -805,21 +880,17 @@ int dirac_step_norm(dirac_ctx *c, int64_t n, void *dev_out, void *stream) {
     const size_t cap_sz = partial_doubles(c) / 2;
     const int cap = cap_sz > 0x7fffffff ? 0x7fffffff : (int)cap_sz;
     const int kc = kernel_choice(c);
-    if (march3_applies(c)) {
+    const bool fp32 = c->dtype == DIRAC_C64;
+    const Route r = fp32 ? route_of<float>(c, n, Op::step_norm) : route_of<double>(c, n, Op::step_norm);
+    if (r.way == Way::march3) {
         rc = upload_tables(c, s);
         if (rc) return rc;
-        March3Plan plan;
-        const int64_t flips = kc == DIRAC_KERNEL_FUSED2 && n >= 2 ? flips_of(c, n - 2) + 1 : flips_of(c, n - 1) + flips_of(c, 1);
-        const bool ok = c->dtype == DIRAC_C64 ? plan_march3<float>(c, n, flips, true, &plan)
-                                              : plan_march3<double>(c, n, flips, true, &plan);
-        if (ok) {
-            int nb = 0;
-            rc = c->dtype == DIRAC_C64 ? run_march3<float>(c, plan, false, s, part, cap, &nb)
-                                       : run_march3<double>(c, plan, false, s, part, cap, &nb);
-            if (rc) return rc;
-            HIPCHK(c, launch_final_sum(part, nb, 2, (double *)dev_out, s));
-            return DIRAC_OK;
-        }
+        int nb = 0;
+        rc = fp32 ? run_march3<float>(c, r.plan, false, s, part, cap, &nb)
+                  : run_march3<double>(c, r.plan, false, s, part, cap, &nb);
+        if (rc) return rc;
+        HIPCHK(c, launch_final_sum(part, nb, 2, (double *)dev_out, s));
+        return DIRAC_OK;
     }
     if (c->ndim == 3 && kc == DIRAC_KERNEL_FUSED2 && n >= 2 && !c->links_on) {
         rc = dirac_step(c, n - 2, stream);
@@ -859,13 +930,11 @@ int dirac_step_norm(dirac_ctx *c, int64_t n, void *dev_out, void *stream) {
         HIPCHK(c, hipMemcpyAsync(dev_out, res + 1, 2 * sizeof(double), hipMemcpyDeviceToDevice, s));
         return DIRAC_OK;
     }
-    bool stepped = false;
-    if (tile2_applies(c)) {
+    const bool stepped = r.way == Way::tile2;
+    if (stepped) {
         rc = upload_tables(c, s);
         if (rc) return rc;
-        const int64_t flips = flips_of(c, n - 1) + flips_of(c, 1);
-        rc = c->dtype == DIRAC_C64 ? run_tile2<float>(c, n, false, flips, s, &stepped)
-                                   : run_tile2<double>(c, n, false, flips, s, &stepped);
+        rc = fp32 ? run_tile2<float>(c, n, false, r.passes, s) : run_tile2<double>(c, n, false, r.passes, s);
         if (rc) return rc;
     }
     if (!stepped) {
@@ -900,6 +969,18 @@ int dirac_step_norm(dirac_ctx *c, int64_t n, void *dev_out, void *stream) {
     rc = dirac_norm_device(c, res, stream);
     if (rc) return rc;
     HIPCHK(c, hipMemcpyAsync(dev_out, res + 1, 2 * sizeof(double), hipMemcpyDeviceToDevice, s));
+    return DIRAC_OK;
+}
+
+int dirac_route(dirac_ctx *c, int64_t n, int call, char *out, size_t len) {
+    if (!c || !out || len == 0) return DIRAC_E_ARG;
+    out[0] = 0;
+    if (c->is_batch) return fail(c, DIRAC_E_STATE, "batch context");
+    if (n < 0 || call < DIRAC_CALL_STEP || call > DIRAC_CALL_STEP_NORM || (call == DIRAC_CALL_STEP_NORM && n < 1))
+        return fail(c, DIRAC_E_ARG, "bad n or call");
+    const std::string t = c->dtype == DIRAC_C64 ? route_text<float>(c, n, (Op)call) : route_text<double>(c, n, (Op)call);
+    if (t.size() >= len) return fail(c, DIRAC_E_SHAPE, "the text takes %zu bytes", t.size() + 1);
+    memcpy(out, t.c_str(), t.size() + 1);
     return DIRAC_OK;
 }
 

@@ -29,6 +29,7 @@
 #pragma once
 
 #include <algorithm>
+#include <iterator>
 #include <type_traits>
 
 #include "device.h"
@@ -150,7 +151,8 @@ __device__ __forceinline__ void march3r(const FusedArgs<R> &a, const R *__restri
 #pragma unroll
             for (int c = 0; c < 2; ++c)
 #pragma unroll
-                for (int k = 0; k < K; ++k) W[l][s][c][k] = zero;    if constexpr (SITE != 0)
+                for (int k = 0; k < K; ++k) W[l][s][c][k] = zero;
+    if constexpr (SITE != 0)
         for (int s = 0; s < 3; ++s)
             for (int c = 0; c < 2; ++c)
                 for (int k = 0; k < K; ++k) {
@@ -441,20 +443,13 @@ __global__ __launch_bounds__(NW * 64, WPE) void k3_march3r(FusedArgs<R> a, const
     }
 }
 
-// A built shape: steps per launch, rows per thread, waves, workgroups a CU holds at
-// once (by LDS), and the measured time of one iteration (half-plane) of a workgroup
-// that has a CU to itself; two on a CU take 1.45 times that each.
+// A built shape: steps per launch, rows per thread, waves, waves per SIMD that its
+// registers allow, workgroups a CU holds at once (by LDS), and the measured time of
+// one iteration (half-plane) of a workgroup that has a CU to itself; two on a CU
+// take 1.45 times that each.
 struct M3Shape {
-    int T, K, NW, occ;
+    int T, K, NW, WPE, occ;
     double iter_us;
-};
-
-// How a launch of T steps runs: shape (-1: none has T), tile width, tiles in y,
-// chunks in z, and its estimated time.
-struct M3Pick {
-    int shape = -1, tw = 0, nty = 0, nzc = 0;
-    bool xp = false;                        // rows wrap within the wave
-    double us = 0.0;
 };
 
 // Tile width: 56 complex64 cells keep every row's stores on whole 64-byte pieces (60
@@ -468,15 +463,15 @@ template <typename R> inline int m3_width(int nx, int T) {
     return (sizeof(R) == 8 || n56 <= 5) && nf < n56 ? full : 56;
 }
 
-// The fastest of `count` shapes for T steps.  A chunk of p planes takes 2 p + 4 T
+// The fastest of a unit's shapes for T steps.  A unit names the precision R, whether
+// per-site records come in (kRec), and its shapes (kShapes).  A chunk of p planes takes 2 p + 4 T
 // iterations, of which the filling ones evaluate few levels: together they cost
 // about 2 (p + T).  Workgroups run in rounds of one or two per CU.  The last pick
 // for each (T, boundary) is kept per thread.  Periodic rows that divide 64
 // need no ring in x: built for the shapes of one row per thread and two steps, which
 // such lattices take (two steps of 64^3 with and without, when added: complex64 17.1
 // and 21 us, complex128 21.7 and 28, with records 28 and 39).
-template <typename R>
-static const M3Pick &m3_pick(const M3Shape *sh, int count, int T, bool zb, int nx, int ny, int nz) {
+template <class U> static const M3Pick &m3_pick(int T, bool zb, int nx, int ny, int nz) {
     struct Memo {
         int nx = -1, ny = -1, nz = -1;
         M3Pick pick;
@@ -486,20 +481,23 @@ static const M3Pick &m3_pick(const M3Shape *sh, int count, int T, bool zb, int n
     if (m.nx == nx && m.ny == ny && m.nz == nz) return m.pick;
     M3Pick best;
     const int64_t cus = resident_per_round();
-    for (int q = 0; q < count; ++q) {
-        if (sh[q].T != T) continue;
+    for (int q = 0; q < (int)std::size(U::kShapes); ++q) {
+        const M3Shape &sh = U::kShapes[q];
+        if (sh.T != T) continue;
         M3Pick p;
         p.shape = q;
-        p.xp = !zb && T == 2 && sh[q].K == 1 && 64 % nx == 0;
-        p.tw = p.xp ? nx : m3_width<R>(nx, T);
-        p.nty = (ny + sh[q].K * sh[q].NW - 2 * T - 1) / (sh[q].K * sh[q].NW - 2 * T);
+        p.K = sh.K;
+        p.NW = sh.NW;
+        p.xp = !zb && T == 2 && sh.K == 1 && 64 % nx == 0;
+        p.tw = p.xp ? nx : m3_width<typename U::R>(nx, T);
+        p.nty = (ny + sh.K * sh.NW - 2 * T - 1) / (sh.K * sh.NW - 2 * T);
         const int64_t tiles = (int64_t)((nx + p.tw - 1) / p.tw) * p.nty;
-        for (int occ = 1; occ <= sh[q].occ; ++occ) {
+        for (int occ = 1; occ <= sh.occ; ++occ) {
             const int64_t per = cus * occ, cap = std::min<int64_t>(nz, 8 * ((per + tiles - 1) / tiles));
             for (int64_t c = 1; c <= cap; ++c) {
                 p.nzc = (int)c;
                 p.us = 4.0 + (double)((tiles * c + per - 1) / per) * 2.0 * (double)((nz + c - 1) / c + T) *
-                                 sh[q].iter_us * (occ == 1 ? 1.0 : 1.45);
+                                 sh.iter_us * (occ == 1 ? 1.0 : 1.45);
                 if (best.shape < 0 || p.us < best.us) best = p;
             }
         }
@@ -552,5 +550,28 @@ hipError_t m3_launch(FusedArgs<R> a, const M3Pick &pick, bool zb, hipStream_t s,
 #undef M3
     return hipGetLastError();
 }
+
+// The launch of a pick among a unit's shapes.
+template <class U, int I = 0>
+hipError_t m3_run(const FusedArgs<typename U::R> &a, const M3Pick &p, bool zb, hipStream_t s, int *nblocks_out) {
+    if constexpr (I < (int)std::size(U::kShapes)) {
+        constexpr M3Shape S = U::kShapes[I];
+        if (p.shape == I)
+            return m3_launch<typename U::R, S.T, S.K, S.NW, S.WPE, U::kRec>(a, p, zb, s, nblocks_out);
+        return m3_run<U, I + 1>(a, p, zb, s, nblocks_out);
+    }
+    return hipErrorInvalidValue;
+}
+
+// What a unit's source file defines.
+#define M3_UNIT(U)                                                                                                  \
+    template <> const M3Pick &march3r_pick_of<U::R, U::kRec>(int steps, bool zb, int nx, int ny, int nz) {          \
+        return m3_pick<U>(steps, zb, nx, ny, nz);                                                                   \
+    }                                                                                                               \
+    template <>                                                                                                     \
+    hipError_t launch_march3r_of<U::R, U::kRec>(const FusedArgs<U::R> &a, int steps, bool zb, hipStream_t s,        \
+                                                int *nblocks_out) {                                                 \
+        return m3_run<U>(a, m3_pick<U>(steps, zb, a.nx, a.ny, a.nz), zb, s, nblocks_out);                           \
+    }
 
 }  // namespace dirac

@@ -4,26 +4,16 @@
 namespace dirac {
 
 namespace {
-// 8 rows, whose 248 registers keep each coefficient from its first use to its second;
-// 12 waves that form it twice measured 227 against 218 us per step at 200 x 168 x 152
-// (206 since, without branches in an iteration).
-constexpr M3Shape kShapes[] = {{1, 2, 8, 1, 5.6}, {2, 1, 8, 1, 2.15}};
-
-const M3Pick &pick(int steps, bool zb, int nx, int ny, int nz) {
-    return m3_pick<double>(kShapes, sizeof(kShapes) / sizeof(kShapes[0]), steps, zb, nx, ny, nz);
-}
+struct Unit {
+    using R = double;
+    static constexpr bool kRec = true;
+    // 8 rows, whose 248 registers keep each coefficient from its first use to its second;
+    // 12 waves that form it twice measured 227 against 218 us per step at 200 x 168 x 152
+    // (206 since, without branches in an iteration).
+    static constexpr M3Shape kShapes[] = {{1, 2, 8, 2, 1, 5.6}, {2, 1, 8, 2, 1, 2.15}};
+};
 }  // namespace
 
-template <> double march3r_us_of<double, true>(int steps, bool zb, int nx, int ny, int nz) {
-    return pick(steps, zb, nx, ny, nz).us;
-}
-
-template <>
-hipError_t launch_march3r_of<double, true>(const FusedArgs<double> &a, int steps, bool zb, hipStream_t s, int *nblocks_out) {
-    const M3Pick &p = pick(steps, zb, a.nx, a.ny, a.nz);
-    if (p.shape == 0) return m3_launch<double, 1, 2, 8, 2, true>(a, p, zb, s, nblocks_out);
-    if (p.shape == 1) return m3_launch<double, 2, 1, 8, 2, true>(a, p, zb, s, nblocks_out);
-    return hipErrorInvalidValue;
-}
+M3_UNIT(Unit)
 
 }  // namespace dirac

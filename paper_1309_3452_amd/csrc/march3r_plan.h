@@ -9,10 +9,21 @@ namespace dirac {
 int resident_per_round();              // workgroups of one per CU (fused2.hip)
 // Most steps of one launch: three only with V(z) tables in complex64.
 inline int march3r_most(bool fp32, bool site) { return fp32 && !site ? 3 : 2; }
-// Estimated microseconds of a launch of `steps` steps (REC: with per-site records).
-template <typename R, bool REC> double march3r_us_of(int steps, bool zb, int nx, int ny, int nz);
+// How a launch of some steps runs: which built shape (-1: none has that many
+// steps) of K rows in each of NW waves, tile width, tiles in y, chunks in z, whether
+// rows wrap within the wave, and its estimated microseconds.
+struct M3Pick {
+    int shape = -1, K = 0, NW = 0, tw = 0, nty = 0, nzc = 0;
+    bool xp = false;
+    double us = 0.0;
+};
+// REC: with per-site records.
+template <typename R, bool REC> const M3Pick &march3r_pick_of(int steps, bool zb, int nx, int ny, int nz);
+template <typename R> const M3Pick &march3r_pick(int steps, bool site, bool zb, int nx, int ny, int nz) {
+    return site ? march3r_pick_of<R, true>(steps, zb, nx, ny, nz) : march3r_pick_of<R, false>(steps, zb, nx, ny, nz);
+}
 template <typename R> double march3r_us(int steps, bool site, bool zb, int nx, int ny, int nz) {
-    return site ? march3r_us_of<R, true>(steps, zb, nx, ny, nz) : march3r_us_of<R, false>(steps, zb, nx, ny, nz);
+    return march3r_pick<R>(steps, site, zb, nx, ny, nz).us;
 }
 // The same for two steps of the LDS march on complex64 lattices of even width
 // (fused2.hip): its workgroups spend about 3.3 us on a plane, 5.4 with records.

@@ -257,6 +257,13 @@ class Lattice:
     def reverse(self, n: int = 1):
         check(lib().dirac_reverse(self._ctx, int(n), _stream_handle()), self._ctx)
 
+    def route(self, n: int = 1, call: str = "step") -> str:
+        """The kernels that step(n), reverse(n) or step_norm(n) would launch (dirac_route)."""
+        code = {"step": 0, "reverse": 1, "step_norm": 2}[call]
+        text = ctypes.create_string_buffer(1024)
+        check(lib().dirac_route(self._ctx, int(n), code, text, len(text)), self._ctx)
+        return text.value.decode()
+
     # -- reductions ----------------------------------------------------------
     def norm(self):
         """(E_r, E_r summed on the C,D / v sites, plain norm) in FP64; synchronous."""

@@ -1,0 +1,76 @@
+"""Which kernels a call would launch (dirac_route), on the CPU: the choice depends on
+the lattice and the call alone (without a device the estimates take 256 CUs, an
+MI355X's)."""
+import ctypes
+
+import pytest
+
+from paper_1309_3452_amd import _abi
+
+C64, C128 = _abi.DIRAC_C64, _abi.DIRAC_C128
+STEP, REVERSE, STEP_NORM = 0, 1, 2
+AUTO, SPLIT, FUSED, FUSED2 = 0, 1, 2, 3
+
+
+def route(shape, dtype, n, call=STEP, site=False, links=False, zero=False, slab=False, kernel=AUTO, shift=None,
+          size=1024):
+    """The route of a context whose arrays (fake pointers, 4 TiB apart) are never touched."""
+    L, c = _abi.lib(), ctypes.c_void_p()
+    flags = (_abi.DIRAC_ZERO_BC if zero else 0) | (_abi.DIRAC_SLAB_Z if slab else 0)
+    nz = shape[2] if len(shape) == 3 else 1
+    assert L.dirac_create(ctypes.byref(c), len(shape), shape[0], shape[1], nz, dtype, 0.5, 1.0, 1.0, 1.0, flags) == 0
+    try:
+        a = [(1 << 50) + (q << 42) for q in range(48)]
+        second = [p + shift for p in a[:8]] if shift is not None else a[8:16]
+        assert L.dirac_bind_state(c, _abi.ptr_array(a[:8]), _abi.ptr_array(second)) == 0
+        if site:
+            assert L.dirac_set_theta_field(c, _abi.ptr_array(a[16:24])) == 0
+        if links:
+            assert L.dirac_set_links(c, _abi.ptr_array(a[24:48])) == 0
+        assert L.dirac_set_kernel(c, kernel, 0, 0) == 0
+        text = ctypes.create_string_buffer(size)
+        rc = L.dirac_route(c, n, call, text, size)
+        return text.value.decode() if rc == 0 else rc
+    finally:
+        L.dirac_destroy(c)
+
+
+def test_explicit_kernels():
+    s = (96, 40, 20)
+    assert route(s, C64, 5, kernel=SPLIT) == "5 x split"
+    assert route(s, C64, 5, kernel=FUSED) == "5 x fused"
+    assert route(s, C64, 5, kernel=FUSED2) == "2 x fused2; 1 x fused"
+    assert route(s, C64, 5, REVERSE, kernel=FUSED2) == "1 x half; 2 x fused2; 1 x half"
+    assert route(s, C128, 3, links=True) == "3 x fused links"
+    assert route(s, C128, 3, REVERSE, links=True) == "3 x split"
+    assert route((64, 64, 16), C128, 2, slab=True) == "1 x march3r steps=2"
+    assert route((64, 64, 16), C64, 2, slab=True) == "1 x fused2"
+    assert route(s, C64, 0) == ""
+
+
+def test_arguments():
+    s = (96, 40, 20)
+    assert route(s, C64, -1) == -1
+    assert route(s, C64, 0, STEP_NORM) == -1
+    assert route(s, C64, 1, 3) == -1
+    assert route(s, C64, 5, size=8) == -2
+    assert _abi.lib().dirac_route(None, 1, 0, ctypes.create_string_buffer(8), 8) == -1
+
+
+@pytest.mark.parametrize("shape", [(70, 40), (20, 9, 12)])
+@pytest.mark.parametrize("dtype,size", [(C64, 8), (C128, 16)])
+def test_sets_that_share_memory_step_in_place(shape, dtype, size):
+    for shift in (0, size, -size, (2 * shape[0] + 1) * size):
+        for call in (STEP, REVERSE):
+            assert route(shape, dtype, 6, call, zero=True, shift=shift) == "6 x split", (shift, call)
+    n = size
+    for q in shape:
+        n *= q
+    assert "split" not in route(shape, dtype, 6, zero=True, shift=n)        # neighbours, not shared
+
+
+def test_tables_beyond_32_bit_offsets():
+    long = ((1 << 25) + 8)
+    assert "march3r" not in route((1, 1, long), C128, 6, zero=True)
+    assert "march3r" in route((1, 1, long), C128, 6, zero=True, site=True)
+    assert "march3r" not in route((1, 1, 2 * long), C64, 6)
