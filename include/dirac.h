@@ -86,9 +86,10 @@ enum dirac_status {
  * summation by parts in the proofs of the Lemmas (Sect. 2, Sect. 3) leaves no
  * boundary terms with zero values outside either, so E_r stays exactly
  * conserved.  Steps run in an even number of ping-pong launches, so the state
- * stays in its buffer set, or on the split kernels (one launch per half-step, in
- * place) for a single step, with DIRAC_KERNEL_SPLIT and where the two sets share
- * an array.  Not combined with DIRAC_SLAB_Z (DIRAC_E_ARG); dirac_set_links and
+ * stays in its buffer set, in place on the split kernels (one launch per half-step)
+ * where those are faster (a single step, and in 3D two or three of most boxes), or a
+ * mix; with DIRAC_KERNEL_SPLIT and where the two sets overlap always in place.  Not
+ * combined with DIRAC_SLAB_Z (DIRAC_E_ARG); dirac_set_links and
  * dirac_adjoint_vz are refused (DIRAC_E_STATE).
  */
 #define DIRAC_ZERO_BC 4u

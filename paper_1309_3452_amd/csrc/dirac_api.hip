@@ -5,6 +5,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -293,38 +294,73 @@ LinkPtrs link_ptrs(const dirac_ctx *c) {
     return L;
 }
 
-// n steps as launches of three, two and one steps, in that order.
+// n steps as `splits` in-place steps of the split kernels (zero values outside only),
+// then launches of three, two and one steps.
 struct March3Plan {
-    int64_t threes = 0, twos = 0, ones = 0;
+    int64_t splits = 0, threes = 0, twos = 0, ones = 0;
+    int64_t launches() const { return threes + twos + ones; }
 };
+
+// Estimated microseconds of a (3+1)D step on the split kernels, and of the functional
+// as a reduction over the state.  A thread costs 22 ps, with a cell or without, a cell
+// at least 33 (complex64) or 64 ps, half as much again where rows start off the
+// 64-byte pieces (not in complex128 up to 30 MB) and 1.42 times from memory rather than
+// the caches; all 1.18 times with records; two launches take 7.8 (9.0) at least.
+// Measured / estimated, zero values outside: complex64 4 x 64 x 512 49 / 50, 33 x 40 x 50
+// 8.7 / 7.8, 128^3 66 / 73, 129^3 109 / 110, 200 x 168 x 152 224 / 243, complex128
+// 63 x 100 x 30 14 / 16, 128^3 124 / 138, 1 x 300 x 300 103 / 130, with records 125 / 153.
+double split3_us(const dirac_ctx *c) {
+    const bool fp32 = c->dtype == DIRAC_C64;
+    const double cells = (double)c->nx * (double)c->ny * (double)c->nz, bytes = cells * (fp32 ? 64.0 : 128.0);
+    const double threads = (double)((c->nx + 63) / 64 * 64) * (double)((c->ny + 3) / 4 * 4) * (double)c->nz;
+    double ps = fp32 ? 33.0 : 64.0;
+    if (c->nx * (fp32 ? 8 : 16) % 64 != 0 && (fp32 || bytes > 3e7)) ps *= 1.5;
+    if (bytes > 3e8) ps *= 1.42;
+    const double us = 1e-6 * std::max(22.0 * threads, ps * cells) * (c->site_mode ? 1.18 : 1.0);
+    return std::max(fp32 ? 7.8 : 9.0, 3.5 + us);
+}
+double norm3_us(const dirac_ctx *c) {
+    return 30.0 + 20e-6 * (double)((c->nx + 63) / 64 * 64) * (double)((c->ny + 3) / 4 * 4) * (double)c->nz;
+}
 
 // The split of n with the least estimated time whose launches have the parity of
 // `flips`; with sum_last its last launch has at most two steps (it also sums the
-// functional).  False if there is none (n = 1, flips even; n = 0).
+// functional, for a fifth of its time more).  With zero values outside in-place steps
+// may come in too: two of them in place of two one-step launches are as fast or faster
+// on boxes of up to about 128^3 (two steps of 128^3 complex64 131 against 151 us, 63 x 100
+// x 30 complex128 28 against 40, 200 x 168 x 152 complex64 448 against 310).  False if
+// there is no plan or in-place steps alone are the fastest (n = 1 with an even number
+// of flips; n = 0).
 template <typename R> bool plan_march3(const dirac_ctx *c, int64_t n, int64_t flips, bool sum_last, March3Plan *out) {
     const int most = march3r_most(sizeof(R) == 4, c->site_mode);
     double us[4] = {};
     for (int t = 1; t <= most; ++t)
         us[t] = march3r_us<R>(t, c->site_mode, c->zbc, (int)c->nx, (int)c->ny, (int)c->nz);
+    const double split = c->zbc ? split3_us(c) : 0.0;
     bool found = false;
-    double best = 0.0;
-    const int64_t lo = (n + most - 1) / most, hi = n / 2 + 3 < n ? n / 2 + 3 : n;
-    for (int64_t p = lo; p <= hi; ++p) {
-        if (p < 1 || ((p ^ flips) & 1)) continue;
-        March3Plan q;
-        if (2 * p >= n) {
-            q.twos = n - p;
-            q.ones = 2 * p - n;
-        } else {
-            q.threes = n - 2 * p;
-            q.twos = 3 * p - n;
-        }
-        if (sum_last && q.twos + q.ones == 0) continue;
-        const double t = (double)q.threes * us[3] + (double)q.twos * us[2] + (double)q.ones * us[1];
-        if (!found || t < best) {
-            found = true;
-            best = t;
-            *out = q;
+    double best = c->zbc ? (double)n * split + (sum_last ? norm3_us(c) : 0.0) : 1e300;
+    for (int64_t splits = 0; splits <= (c->zbc ? 3 : 0); ++splits) {
+        const int64_t m = n - splits;
+        const int64_t lo = (m + most - 1) / most, hi = m / 2 + 3 < m ? m / 2 + 3 : m;
+        for (int64_t p = lo; p <= hi; ++p) {
+            if (p < 1 || ((p ^ flips) & 1)) continue;
+            March3Plan q;
+            q.splits = splits;
+            if (2 * p >= m) {
+                q.twos = m - p;
+                q.ones = 2 * p - m;
+            } else {
+                q.threes = m - 2 * p;
+                q.twos = 3 * p - m;
+            }
+            if (sum_last && q.twos + q.ones == 0) continue;
+            const double t = (double)splits * split + (double)q.threes * us[3] + (double)q.twos * us[2] +
+                             (double)q.ones * us[1] + (sum_last ? 0.2 * us[q.ones ? 1 : 2] : 0.0);
+            if (t < best) {
+                found = true;
+                best = t;
+                *out = q;
+            }
         }
     }
     return found;
@@ -398,7 +434,10 @@ bool ones_on_fused(const dirac_ctx *c) { return !c->zbc && (c->dtype == DIRAC_C1
 // last one sums the functional and *nblocks receives its workgroups.
 template <typename R>
 int run_march3(dirac_ctx *c, const March3Plan &plan, bool rev, hipStream_t s, double *npart, int npart_cap, int *nblocks) {
-    const int64_t p = plan.threes + plan.twos + plan.ones;
+    for (int64_t t = 0; t < plan.splits; ++t)
+        for (int which = 0; which < 2; ++which)        // A,B then C,D; reversed steps in between are H1' H2' too
+            HIPCHK(c, launch_half3<R>(half_args<R>(c, rev), which, c->site_mode, s));
+    const int64_t p = plan.launches();
     for (int64_t t = 0; t < p; ++t) {
         FusedArgs<R> a = rev ? fused_args_rev<R>(c) : fused_args<R>(c);
         if (npart && t + 1 == p) {
@@ -537,6 +576,7 @@ template <typename R> std::string route_text(const dirac_ctx *c, int64_t n, Op o
                     tile2_rows(tile2_best_shape(steps, 1, &c->nx, &c->ny, fp32, kind, &us)));
         }
     } else if (r.way == Way::march3) {
+        add(r.plan.splits, "%s", "split");
         const int64_t counts[4] = {0, r.plan.ones, r.plan.twos, r.plan.threes};
         for (int T = 3; T > 0; --T) {
             if (counts[T] == 0) continue;

@@ -464,13 +464,18 @@ template <typename R> inline int m3_width(int nx, int T) {
 }
 
 // The fastest of a unit's shapes for T steps.  A unit names the precision R, whether
-// per-site records come in (kRec), and its shapes (kShapes).  A chunk of p planes takes 2 p + 4 T
-// iterations, of which the filling ones evaluate few levels: together they cost
-// about 2 (p + T).  Workgroups run in rounds of one or two per CU.  The last pick
-// for each (T, boundary) is kept per thread.  Periodic rows that divide 64
-// need no ring in x: built for the shapes of one row per thread and two steps, which
-// such lattices take (two steps of 64^3 with and without, when added: complex64 17.1
-// and 21 us, complex128 21.7 and 28, with records 28 and 39).
+// per-site records come in (kRec), and its shapes (kShapes).  A chunk of p planes
+// takes 2 p + 4 T iterations, of which the filling ones evaluate few levels: together
+// they cost about 2 (p + T).  Workgroups run in rounds of one or two per CU.  A
+// one-step launch with zero values outside, whose lanes without a cell load nothing,
+// fills sooner and takes less where a tile is partly empty, but no less than its bytes
+// at 8 TB/s out of the caches and 4.3 from memory.  Measured / estimated: complex64
+// 128^3 75 / 76 us, 300 x 1 x 300 33 / 39, with records 128^3 99 / 98, 63 x 100 x 30 18 / 16,
+// complex128 128^3 122 / 142, 63 x 100 x 30 20 / 21, 4 x 64 x 512 41 / 51.
+// The last pick for each (T, boundary) is kept per thread.  Periodic rows that divide
+// 64 need no ring in x: built for the shapes of one row per thread and two steps,
+// which such lattices take (two steps of 64^3 with and without, when added: complex64
+// 17.1 and 21 us, complex128 21.7 and 28, with records 28 and 39).
 template <class U> static const M3Pick &m3_pick(int T, bool zb, int nx, int ny, int nz) {
     struct Memo {
         int nx = -1, ny = -1, nz = -1;
@@ -492,15 +497,22 @@ template <class U> static const M3Pick &m3_pick(int T, bool zb, int nx, int ny, 
         p.tw = p.xp ? nx : m3_width<typename U::R>(nx, T);
         p.nty = (ny + sh.K * sh.NW - 2 * T - 1) / (sh.K * sh.NW - 2 * T);
         const int64_t tiles = (int64_t)((nx + p.tw - 1) / p.tw) * p.nty;
+        const double full = (double)nx * ny / ((double)tiles * p.tw * (sh.K * sh.NW - 2 * T));
+        const bool partly = T == 1 && zb;
+        const double iter_us = sh.iter_us * (partly ? 0.4 + 0.72 * full : 1.0), filling = partly ? 0.3 : T;
         for (int occ = 1; occ <= sh.occ; ++occ) {
             const int64_t per = cus * occ, cap = std::min<int64_t>(nz, 8 * ((per + tiles - 1) / tiles));
             for (int64_t c = 1; c <= cap; ++c) {
                 p.nzc = (int)c;
-                p.us = 4.0 + (double)((tiles * c + per - 1) / per) * 2.0 * (double)((nz + c - 1) / c + T) *
-                                 sh.iter_us * (occ == 1 ? 1.0 : 1.45);
+                p.us = 4.0 + (double)((tiles * c + per - 1) / per) * 2.0 * ((double)((nz + c - 1) / c) + filling) *
+                                 iter_us * (occ == 1 ? 1.0 : 1.45);
                 if (best.shape < 0 || p.us < best.us) best = p;
             }
         }
+    }
+    if (T == 1 && zb) {
+        const double bytes = (double)nx * ny * nz * 8.0 * sizeof(typename U::R) * (!U::kRec ? 4.0 : sizeof(typename U::R) == 4 ? 6.0 : 5.0);
+        best.us = std::max(best.us, 4.0 + bytes / (bytes > 2e8 ? 4.3e6 : 8e6));
     }
     m.nx = nx;
     m.ny = ny;

@@ -57,7 +57,7 @@ def test_arguments():
     assert _abi.lib().dirac_route(None, 1, 0, ctypes.create_string_buffer(8), 8) == -1
 
 
-@pytest.mark.parametrize("shape", [(70, 40), (20, 9, 12)])
+@pytest.mark.parametrize("shape", [(70, 40), (120, 90, 70)])
 @pytest.mark.parametrize("dtype,size", [(C64, 8), (C128, 16)])
 def test_sets_that_share_memory_step_in_place(shape, dtype, size):
     for shift in (0, size, -size, (2 * shape[0] + 1) * size):
@@ -66,11 +66,29 @@ def test_sets_that_share_memory_step_in_place(shape, dtype, size):
     n = size
     for q in shape:
         n *= q
-    assert "split" not in route(shape, dtype, 6, zero=True, shift=n)        # neighbours, not shared
+    apart = route(shape, dtype, 6, zero=True, shift=n)                       # neighbours, not shared
+    assert "tile2" in apart or "march3r" in apart, apart
 
 
 def test_tables_beyond_32_bit_offsets():
     long = ((1 << 25) + 8)
     assert "march3r" not in route((1, 1, long), C128, 6, zero=True)
-    assert "march3r" in route((1, 1, long), C128, 6, zero=True, site=True)
     assert "march3r" not in route((1, 1, 2 * long), C64, 6)
+    assert "march3r" in route((1, 1, long), C64, 6)
+
+
+@pytest.mark.parametrize("shape,dtype,n,call,expect", [
+    # two one-step launches took longer than two steps in place
+    ((128, 128, 128), C64, 2, STEP, "2 x split"), ((33, 40, 50), C64, 2, STEP, "2 x split"),
+    ((63, 100, 30), C128, 2, STEP, "2 x split"), ((64, 512, 4), C128, 2, STEP, "2 x split"),
+    # so did any launches where tiles are nearly empty
+    ((300, 1, 300), C64, 3, STEP, "3 x split"), ((300, 1, 300), C64, 4, REVERSE, "4 x split"),
+    ((512, 4, 64), C128, 3, STEP, "3 x split"),
+    # an odd step apart from an even number of launches
+    ((128, 128, 128), C64, 5, STEP, "1 x split; 2 x march3r steps=2"),
+    # larger boxes keep the march
+    ((200, 168, 152), C64, 2, STEP, "2 x march3r steps=1"), ((200, 168, 152), C128, 8, STEP, "4 x march3r steps=2"),
+    ((224, 192, 256), C64, 10, STEP_NORM, "2 x march3r steps=3")])
+def test_zero_boundary_plans(shape, dtype, n, call, expect):
+    r = route(shape, dtype, n, call, zero=True)
+    assert r == expect or "march3r" in expect and r.startswith(expect), r
