@@ -257,6 +257,12 @@ bool offsets_fit(const dirac_ctx *c) {
     return plane < (1ull << 32) && (c->site_mode || tab_bytes_of(c) < (1ull << 32));
 }
 
+bool narrow_on_lds(const dirac_ctx *c) {
+    if (c->dtype != DIRAC_C128 || c->site_mode || c->zbc || c->nx > 16) return false;
+    const int nx = (int)c->nx, ny = (int)c->ny, nz = (int)c->nz;
+    return march_lds_wins_narrow(march3r_us<double>(2, false, false, nx, ny, nz), nx, ny, nz);
+}
+
 // (3+1)D likewise: the register march (march3r.h) where it is the fastest kernel.
 // Per launch of two steps, next to the LDS march (one-step one for an odd
 // complex64 width, split kernels with zero values outside): complex128 256^3
@@ -270,12 +276,20 @@ bool offsets_fit(const dirac_ctx *c) {
 bool march3_applies(const dirac_ctx *c) {
     if (c->ndim != 3 || c->kernel != DIRAC_KERNEL_AUTO || c->tile_y != 0 || c->zchunk != 0 || c->links_on || c->zh)
         return false;
-    if (!offsets_fit(c)) return false;
+    if (!offsets_fit(c) || narrow_on_lds(c)) return false;
     if (!c->zbc && c->dtype == DIRAC_C64 && c->nx % 2 == 0) {
         const int nx = (int)c->nx, ny = (int)c->ny, nz = (int)c->nz;
         if (march3r_us<float>(2, c->site_mode, false, nx, ny, nz) > 0.95 * march_lds_us(c->site_mode, nx, ny, nz)) return false;
     }
     return !sets_shared(c);
+}
+
+// Two steps of a z-slab in one launch: complex128 slabs take the register march too,
+// whose two-step reach is the slab's two halo planes (512 x 512 x 64: 0.90 against 1.08
+// ms, with records 1.45 against 1.91).
+bool slab_on_march3(const dirac_ctx *c) {
+    return c->ndim == 3 && c->zh && c->dtype == DIRAC_C128 && c->kernel == DIRAC_KERNEL_AUTO && c->zchunk == 0 &&
+           !narrow_on_lds(c);
 }
 
 // z-slab mode: the most steps one call may advance between halo refills
@@ -427,8 +441,11 @@ template <typename R> FusedArgs<R> fused_args_rev(dirac_ctx *c) {
 }
 
 // A plan's one-step launches take the LDS march's one-step kernel where its rows are
-// whole (257^3 complex128: 0.84 against 0.97 ms).
-bool ones_on_fused(const dirac_ctx *c) { return !c->zbc && (c->dtype == DIRAC_C128 || c->nx % 2 == 0); }
+// whole (257^3 complex128: 0.84 against 0.97 ms), and in a single row of them (301 x 1 x
+// 300 complex64 26 against 29 us; with records level).
+bool ones_on_fused(const dirac_ctx *c) {
+    return !c->zbc && (c->dtype == DIRAC_C128 || c->nx % 2 == 0 || (c->ny == 1 && !c->site_mode));
+}
 
 // The launches of a plan, forward or of the reversed sequence; with npart the
 // last one sums the functional and *nblocks receives its workgroups.
@@ -491,15 +508,9 @@ template <typename R> int run_tile2(dirac_ctx *c, int64_t n, bool reverse, int64
     return DIRAC_OK;
 }
 
-// Two steps of a (3+1)D lattice or z-slab in one launch: in complex128 a slab takes
-// the register march too, whose two-step reach is the slab's two halo planes
-// (512 x 512 x 64: 0.90 against 1.08 ms, with records 1.45 against 1.91).
-template <typename R> bool two_on_march3(const dirac_ctx *c) {
-    return sizeof(R) == 8 && c->ndim == 3 && c->zh && c->kernel == DIRAC_KERNEL_AUTO && c->zchunk == 0;
-}
+// Two steps of a (3+1)D lattice or z-slab in one launch.
 template <typename R> hipError_t launch_two(const dirac_ctx *c, const FusedArgs<R> &a, hipStream_t s, int *nblocks) {
-    if (two_on_march3<R>(c))
-        return launch_march3r<R>(a, 2, c->site_mode, false, s, nblocks);
+    if (slab_on_march3(c)) return launch_march3r<R>(a, 2, c->site_mode, false, s, nblocks);
     return launch_fused3x2<R>(a, c->site_mode, s, nblocks);
 }
 
@@ -589,7 +600,7 @@ template <typename R> std::string route_text(const dirac_ctx *c, int64_t n, Op o
                 p.xp ? " rotating" : "");
         }
     } else {
-        if (r.way == Way::fused2) add(m / 2, "%s", two_on_march3<R>(c) ? "march3r steps=2" : "fused2");
+        if (r.way == Way::fused2) add(m / 2, "%s", slab_on_march3(c) ? "march3r steps=2" : "fused2");
         if (r.way == Way::fused2) m &= 1;
         add(m, "%s", r.way == Way::split ? "split" : c->links_on ? "fused links" : "fused");
     }

@@ -33,6 +33,19 @@ inline double march_lds_us(bool site, int nx, int ny, int nz) {
     return 2.0 + (double)((tiles * nzc + cus - 1) / cus) * ((nz + nzc - 1) / nzc + 6) *
                      (site ? 5.4 : 3.3);
 }
+// And on complex128 lattices with V(z) tables of at most 16 columns, half a tile of the
+// LDS march: its planes take 2.0 us there, 2.4 with 16 columns (3.5 to 4.4 with more),
+// where a register march iteration costs much the same whatever the row holds.  Two
+// steps, LDS / register march: 1 x 200 x 200 50 / 72 us, 8 x 200 x 200 55 / 72, 16 x 200 x 200
+// 62 / 72, 20 x 200 x 200 102 / 80; 1 x 64 x 256 29 / 36, 1 x 7 x 600 24 / 18.  The register
+// march's estimate is a third above its time on such rows.
+inline bool march_lds_wins_narrow(double march_us, int nx, int ny, int nz) {
+    if (nx > 16) return false;
+    const int64_t tiles = (ny + 7) / 8, cus = resident_per_round();
+    const int nzc = pick_chunks(tiles, nz, 6);
+    const double plane = 2.0 + 0.05 * (nx > 8 ? nx - 8 : 0);
+    return 2.0 + (double)((tiles * nzc + cus - 1) / cus) * ((nz + nzc - 1) / nzc + 6) * plane < 0.75 * march_us;
+}
 // One launch of `steps` steps, in -> out, forward or (a.rev) of the reversed
 // sequence.  With a.npart (one or two steps, forward) the per-workgroup sums of
 // the functional go there.

@@ -92,3 +92,19 @@ def test_tables_beyond_32_bit_offsets():
 def test_zero_boundary_plans(shape, dtype, n, call, expect):
     r = route(shape, dtype, n, call, zero=True)
     assert r == expect or "march3r" in expect and r.startswith(expect), r
+
+
+def test_narrow_complex128_rows_keep_the_lds_march():
+    for shape in ((1, 300, 300), (4, 64, 512), (12, 200, 200), (16, 200, 200)):
+        assert route(shape, C128, 9) == "4 x fused2; 1 x fused", shape
+        assert route(shape, C128, 9, REVERSE) == "1 x half; 4 x fused2; 1 x half", shape
+        assert "march3r" in route(shape, C128, 9, site=True), shape
+    for shape in ((1, 7, 600), (20, 200, 200), (64, 200, 200)):
+        assert "4 x march3r" in route(shape, C128, 9), shape
+    assert route((8, 200, 200), C128, 2, slab=True) == "1 x fused2"
+
+
+def test_one_step_of_a_single_odd_row():
+    assert route((301, 1, 300), C64, 1) == "1 x fused"
+    assert "march3r" in route((301, 1, 300), C64, 1, site=True)
+    assert "march3r" in route((301, 2, 300), C64, 1)
