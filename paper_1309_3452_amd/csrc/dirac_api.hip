@@ -380,6 +380,43 @@ template <typename R> bool plan_march3(const dirac_ctx *c, int64_t n, int64_t fl
     return found;
 }
 
+// Estimated microseconds of n (2+1)D steps on the kernels before the register tiles:
+// in place on the split kernels (zero values outside, reversed steps) or, up to 8 rows,
+// by row marches.  Split: a thread costs 10.5 ps, a cell at least 20 (complex64) or 36
+// ps, 23 and 39 from memory, 0.85 of that without records.  Marches: a cell of one step
+// 18 ps in complex64 without a potential, the others as in the table; two steps in one
+// launch 1.35 times one.  Measured / estimated per step: in place 100000 x 5 complex64 per
+// site 11 / 12 us, complex128 19 / 20, 400000 x 1 complex128 13 / 19, 8 x 100000 73 / 69; marches
+// 400000 x 1 complex64 12 / 12, 400000 x 4 33 / 34, complex128 per site 75 / 72, with links
+// 99 / 101.
+double before_tiles_us(const dirac_ctx *c, int64_t n, bool in_place) {
+    const bool fp32 = c->dtype == DIRAC_C64;
+    const double cells = (double)c->nx * (double)c->ny;
+    if (in_place) {
+        const double threads = (double)((c->nx + 63) / 64 * 64) * (double)((c->ny + 3) / 4 * 4);
+        const bool far = cells * (fp32 ? 32.0 : 64.0) > 2e8;
+        const double ps = (fp32 ? (far ? 23.0 : 20.0) : (far ? 39.0 : 36.0)) * (c->site_mode ? 1.0 : 0.85);
+        return (double)n * std::max(6.9, 2.0 + 1e-6 * std::max(10.5 * threads, ps * cells));
+    }
+    if (c->ny > 8) return 1e300;
+    constexpr double ps[2][4] = {{36.0, 42.0, 60.0, 66.0}, {18.0, 22.0, 30.0, 34.0}};
+    const double one = std::max(6.4, 5.0 + 1e-6 * ps[fp32 ? 1 : 0][tile2_kind(c->site_mode, c->links_on)] * cells);
+    if (kernel_choice(c) != DIRAC_KERNEL_FUSED2) return (double)n * one;
+    return (double)(n / 2) * 1.35 * one + (double)(n & 1) * one;
+}
+
+// Whether that many passes of register tiles are the faster way.  Up to a round and a
+// half of tiles they are.  Beyond, a few long rows leave a region mostly empty
+// (one step of 400000 x 1 complex128 per site 76 against 21 us, of 400000 x 4 95 against
+// 75, of 400000 x 12 183 against 179; two in place of 100000 x 2 with zero values
+// outside 38 against 16), and so do narrow planes of complex128 records in place
+// (8 x 100000, two steps 171 against 145).
+bool tiles_win(const dirac_ctx *c, int64_t n, int64_t passes, bool in_place) {
+    if (2 * tile2_tiles(0, 1, c->nx, c->ny) <= 3 * (int64_t)resident_per_round()) return true;
+    return tile2_total_us(n, passes, c->nx, c->ny, c->dtype == DIRAC_C64, tile2_kind(c->site_mode, c->links_on)) <=
+           before_tiles_us(c, n, in_place);
+}
+
 // What a call launches, decided here for the call itself and for dirac_route.
 enum class Op { step, reverse, step_norm };
 enum class Way { split, fused, fused2, tile2, march3 };
@@ -405,7 +442,7 @@ template <typename R> Route route_of(const dirac_ctx *c, int64_t n, Op op) {
     if (tile2_applies(c) && !(op == Op::reverse && c->links_on)) {
         r.passes = tile2_passes(n, (int)(flips & 1), 1, &c->nx, &c->ny, sizeof(R) == 4,
                                 tile2_kind(c->site_mode, c->links_on));
-        if (r.passes > 0) {
+        if (r.passes > 0 && tiles_win(c, n, r.passes, c->zbc || op == Op::reverse)) {
             r.way = Way::tile2;
             return r;
         }

@@ -16,6 +16,9 @@ int64_t tile2_tiles(int shape, int ring, int64_t nx, int64_t ny);
 double tile2_pass_us(int shape, int steps, int64_t tiles, double cells, bool fp32, int kind);
 // the fastest shape for a pass of `steps` over `count` lattices, and its time
 int tile2_best_shape(int steps, int64_t count, const int64_t *nx, const int64_t *ny, bool fp32, int kind, double *us);
+// estimated microseconds of n steps in that many passes, the loads of whole regions
+// counted (see tile2.hip)
+double tile2_total_us(int64_t n, int64_t passes, int64_t nx, int64_t ny, bool fp32, int kind);
 // passes for n steps with the parity of `parity`; 0 if there is no such split
 int64_t tile2_passes(int64_t n, int parity, int64_t count, const int64_t *nx, const int64_t *ny, bool fp32, int kind);
 template <typename R> hipError_t launch_tile2(const FusedArgs<R> &a, bool site, bool zb, int steps, hipStream_t s);

@@ -108,3 +108,21 @@ def test_one_step_of_a_single_odd_row():
     assert route((301, 1, 300), C64, 1) == "1 x fused"
     assert "march3r" in route((301, 1, 300), C64, 1, site=True)
     assert "march3r" in route((301, 2, 300), C64, 1)
+
+
+@pytest.mark.parametrize("shape,dtype,n,call,kw,tiles", [
+    # a few very long rows leave the tiles' regions mostly empty
+    ((400000, 1), C128, 1, STEP, dict(site=True), False), ((400000, 1), C64, 7, STEP, {}, False),
+    ((400000, 4), C128, 1, STEP, dict(site=True), False), ((400000, 4), C128, 1, STEP, dict(links=True), False),
+    ((100000, 2), C128, 2, STEP, dict(site=True, zero=True), False),
+    ((100000, 2), C128, 3, REVERSE, dict(site=True), False), ((100000, 1), C64, 1, STEP, {}, False),
+    ((8, 100000), C128, 2, STEP, dict(site=True, zero=True), False),
+    # more steps, more rows or fewer tiles than rounds: tiles
+    ((400000, 4), C128, 7, STEP, dict(site=True), True), ((400000, 12), C128, 1, STEP, dict(site=True), True),
+    ((100000, 2), C64, 9, STEP, {}, True), ((5000, 1), C64, 1, STEP, {}, True),
+    ((8, 100000), C64, 2, STEP, dict(site=True, zero=True), True), ((3000, 3000), C128, 2, STEP, dict(zero=True, site=True), True),
+    ((1024, 512), C64, 100, STEP, dict(site=True), True), ((128, 128), C128, 200, STEP, {}, True),
+    ((333, 1000), C128, 4, REVERSE, dict(site=True), True), ((64, 64), C64, 2, STEP_NORM, {}, True)])
+def test_planes_that_tiles_fit(shape, dtype, n, call, kw, tiles):
+    r = route(shape, dtype, n, call, **kw)
+    assert ("tile2" in r) == tiles, r
