@@ -337,6 +337,13 @@ double norm3_us(const dirac_ctx *c) {
     return 30.0 + 20e-6 * (double)((c->nx + 63) / 64 * 64) * (double)((c->ny + 3) / 4 * 4) * (double)c->nz;
 }
 
+// A plan's one-step launches take the LDS march's one-step kernel where its rows are
+// whole (257^3 complex128: 0.84 against 0.97 ms), and in a single row of them (301 x 1 x
+// 300 complex64 26 against 29 us; with records level).
+bool ones_on_fused(const dirac_ctx *c) {
+    return !c->zbc && (c->dtype == DIRAC_C128 || c->nx % 2 == 0 || (c->ny == 1 && !c->site_mode));
+}
+
 // The split of n with the least estimated time whose launches have the parity of
 // `flips`; with sum_last its last launch has at most two steps (it also sums the
 // functional, for a fifth of its time more).  With zero values outside in-place steps
@@ -348,8 +355,10 @@ double norm3_us(const dirac_ctx *c) {
 template <typename R> bool plan_march3(const dirac_ctx *c, int64_t n, int64_t flips, bool sum_last, March3Plan *out) {
     const int most = march3r_most(sizeof(R) == 4, c->site_mode);
     double us[4] = {};
+    const int nx = (int)c->nx, ny = (int)c->ny, nz = (int)c->nz;
     for (int t = 1; t <= most; ++t)
-        us[t] = march3r_us<R>(t, c->site_mode, c->zbc, (int)c->nx, (int)c->ny, (int)c->nz);
+        us[t] = t == 1 && ones_on_fused(c) ? fused3_us(sizeof(R) == 4, c->site_mode, nx, ny, nz)
+                                           : march3r_us<R>(t, c->site_mode, c->zbc, nx, ny, nz);
     const double split = c->zbc ? split3_us(c) : 0.0;
     bool found = false;
     double best = c->zbc ? (double)n * split + (sum_last ? norm3_us(c) : 0.0) : 1e300;
@@ -475,13 +484,6 @@ template <typename R> FusedArgs<R> fused_args_rev(dirac_ctx *c) {
     if (!c->site_mode) a.tab = (const R *)scratch_at(c, off_tab(c) + align256(tab_bytes<R>(c)));
     a.rev = 1;
     return a;
-}
-
-// A plan's one-step launches take the LDS march's one-step kernel where its rows are
-// whole (257^3 complex128: 0.84 against 0.97 ms), and in a single row of them (301 x 1 x
-// 300 complex64 26 against 29 us; with records level).
-bool ones_on_fused(const dirac_ctx *c) {
-    return !c->zbc && (c->dtype == DIRAC_C128 || c->nx % 2 == 0 || (c->ny == 1 && !c->site_mode));
 }
 
 // The launches of a plan, forward or of the reversed sequence; with npart the

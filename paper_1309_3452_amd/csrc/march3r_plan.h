@@ -33,6 +33,20 @@ inline double march_lds_us(bool site, int nx, int ny, int nz) {
     return 2.0 + (double)((tiles * nzc + cus - 1) / cus) * ((nz + nzc - 1) / nzc + 6) *
                      (site ? 5.4 : 3.3);
 }
+// One step of the LDS march's one-step kernel (fused.hip), rows of even width or
+// complex128: its workgroups spend 4.3 us (complex128 3.8) on a plane of empty tiles and
+// 2.6 (2.8) more on one of full ones, with records 4.9 (4.6) and 4.6 (5.0) more, and fill
+// their pipeline in 10.  Measured / estimated: complex64 16 x 200 x 200 107 / 104 us, 70^3
+// 28 / 29, 128^3 68 / 67, 200 x 168 x 152 181 / 176, with records 241 / 233, complex128
+// 33 x 40 x 50 15 / 17, 200 x 168 x 152 319 / 317, with records 441 / 446.
+inline double fused3_us(bool fp32, bool site, int nx, int ny, int nz) {
+    const int w = fp32 ? 128 : 64;
+    const int64_t tiles = (int64_t)((nx + w - 1) / w) * ((ny + 7) / 8), cus = resident_per_round();
+    const int nzc = pick_chunks(tiles, nz, 3);
+    const double full = (double)nx * ny / ((double)tiles * w * 8);
+    const double plane = site ? (fp32 ? 4.9 + 4.6 * full : 4.6 + 5.0 * full) : (fp32 ? 4.3 + 2.6 * full : 3.8 + 2.8 * full);
+    return 2.0 + (double)((tiles * nzc + cus - 1) / cus) * (((nz + nzc - 1) / nzc) * plane + 10.0);
+}
 // And on complex128 lattices with V(z) tables of at most 16 columns, half a tile of the
 // LDS march: its planes take 2.0 us there, 2.4 with 16 columns (3.5 to 4.4 with more),
 // where a register march iteration costs much the same whatever the row holds.  Two

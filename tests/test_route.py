@@ -126,3 +126,10 @@ def test_one_step_of_a_single_odd_row():
 def test_planes_that_tiles_fit(shape, dtype, n, call, kw, tiles):
     r = route(shape, dtype, n, call, **kw)
     assert ("tile2" in r) == tiles, r
+
+
+def test_one_step_launches_are_priced_as_what_runs():
+    """Periodic complex64 of even width: an odd step runs on the LDS march's one-step
+    kernel, whose time and not the register march's decides against threes."""
+    assert route((40, 135, 81), C64, 11).startswith("3 x march3r steps=3 ")      # 149 -> 138 us
+    assert route((24, 305, 284), C64, 11).startswith("3 x march3r steps=3 ")     # 729 -> 641 us
