@@ -535,10 +535,14 @@ hipError_t m3_launch(FusedArgs<R> a, const M3Pick &pick, bool zb, hipStream_t s,
     const bool norm = a.npart != nullptr;
     if (norm && (nblk > a.npart_cap || a.rev || T > 2)) return hipErrorInvalidValue;
     const dim3 g((unsigned)nblk), b(NW * 64);
+    // one step of a periodic complex128 lattice runs on the LDS march's kernel
+    constexpr bool PERIODIC = T > 1 || sizeof(R) == 4;
 #define M3(SITE, ZB, NORM)                                                                                          \
     do {                                                                                                            \
         constexpr bool XP = !ZB && T == 2 && K == 1;                                                                \
-        if (XP && pick.xp)                                                                                          \
+        if constexpr (!ZB && !PERIODIC)                                                                             \
+            return hipErrorInvalidValue;                                                                            \
+        else if (XP && pick.xp)                                                                                     \
             hipLaunchKernelGGL((k3_march3r<R, T, K, NW, WPE, SITE, ZB, NORM, XP>), g, b, 0, s, a, a.tab, tw);       \
         else                                                                                                        \
             hipLaunchKernelGGL((k3_march3r<R, T, K, NW, WPE, SITE, ZB, NORM, false>), g, b, 0, s, a, a.tab, tw);    \
