@@ -436,6 +436,11 @@ int dirac_adjoint_vz(dirac_ctx *ctx, int64_t n, void *const lam[], void *dLdV_in
 int dirac_adjoint_vz_work(dirac_ctx *ctx, int64_t n, void *const lam[], void *const work[], void *dLdV_int,
                           void *dLdV_half, void *stream);
 
+/* *uses = 1 if dirac_adjoint_vz_work over n steps would use work arrays (the lattice is
+ * large enough to gain, its state bound and n >= 2), else 0: a caller need not allocate
+ * them then.  Makes no HIP call; DIRAC_E_ARG for null arguments. */
+int dirac_adjoint_uses_work(const dirac_ctx *ctx, int64_t n, int *uses);
+
 /* The gradient of the region probability L = sum_{z_s >= z0} |psi_s|^2 after n
  * steps with respect to V(z): dirac_seed_region(ctx, z0, lam) then
  * dirac_adjoint_vz(ctx, n, lam, dLdV_int, dLdV_half).  lam: caller-owned work

@@ -33,7 +33,7 @@ EXPORTS = (
     "dirac_coef_from_theta_c", "dirac_set_links", "dirac_coef_from_fields", "dirac_set_mass",
     "dirac_set_potential_z", "dirac_adjoint", "dirac_autotune", "dirac_coef_from_theta_host",
     "dirac_norm_device_static", "dirac_batch_create_dt", "dirac_stream_copy", "dirac_adjoint_vz_work",
-    "dirac_route",
+    "dirac_route", "dirac_adjoint_uses_work",
 )
 
 
@@ -81,6 +81,7 @@ def lib():
         "dirac_seed_region": ([P, D, PP, P], I),
         "dirac_adjoint_vz": ([P, I64, PP, P, P, P], I),
         "dirac_adjoint_vz_work": ([P, I64, PP, PP, P, P, P], I),
+        "dirac_adjoint_uses_work": ([P, I64, ctypes.POINTER(I)], I),
         "dirac_route": ([P, I64, I, ctypes.c_char_p, ctypes.c_size_t], I),
         "dirac_adjoint": ([P, I64, PP, D, P, P, P], I),
         "dirac_set_mass": ([P, D], I),

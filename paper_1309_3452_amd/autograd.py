@@ -17,10 +17,12 @@ def potential_gradient(lat: Lattice, state0, m: float, v_int, v_half, nsteps: in
     lat.step(nsteps)
     loss = lat.observables(z0)[0]
     lam = lat.seed_region(z0)
-    try:
-        work = [torch.empty_like(t) for t in lam]      # one launch per backward step
-    except torch.cuda.OutOfMemoryError:
-        work = None                                    # no room: in place
+    work = None                                            # in place
+    if lat.adjoint_uses_work(nsteps):
+        try:
+            work = [torch.empty_like(t) for t in lam]      # one launch per backward step
+        except torch.cuda.OutOfMemoryError:
+            work = None                                    # no room
     dvi, dvh = lat.adjoint_vz(nsteps, lam, work)
     return loss, dvi, dvh
 

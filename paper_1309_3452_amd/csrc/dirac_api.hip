@@ -665,6 +665,14 @@ template <typename R> ReduceArgs<R> reduce_args(dirac_ctx *c, double z0) {
     return a;
 }
 
+// Backward steps of the adjoint as one launch each, two at a time, given arrays to
+// ping-pong with.
+bool adjoint_on_march(const dirac_ctx *c, int64_t n) {
+    if (c->ndim != 3 || c->site_mode || c->links_on || c->zh || c->zbc || !c->w_int.empty() || n < 2) return false;
+    return offsets_fit(c) && !sets_shared(c) &&
+           adj_march_wins(c->dtype == DIRAC_C64, (int)c->nx, (int)c->ny, (int)c->nz);
+}
+
 int check_ready(dirac_ctx *c, bool need_scratch) {
     if (!c) return DIRAC_E_ARG;
     if (c->is_batch) return fail(c, DIRAC_E_STATE, "batch context: use the dirac_batch_* calls");
@@ -1166,6 +1174,12 @@ int dirac_adjoint_vz(dirac_ctx *c, int64_t n, void *const lam[], void *dLdV_int,
     return dirac_adjoint_vz_work(c, n, lam, nullptr, dLdV_int, dLdV_half, stream);
 }
 
+int dirac_adjoint_uses_work(const dirac_ctx *c, int64_t n, int *uses) {
+    if (!c || !uses) return DIRAC_E_ARG;
+    *uses = !c->is_batch && c->bound && adjoint_on_march(c, n) ? 1 : 0;
+    return DIRAC_OK;
+}
+
 int dirac_adjoint_vz_work(dirac_ctx *c, int64_t n, void *const lam[], void *const work[], void *dLdV_int,
                           void *dLdV_half, void *stream) {
     int rc = check_ready(c, true);
@@ -1194,8 +1208,7 @@ int dirac_adjoint_vz_work(dirac_ctx *c, int64_t n, void *const lam[], void *cons
                 return fail(c, DIRAC_E_ARG, "lam array %d overlaps a state array", q);
         }
     }
-    const bool march = work && offsets_fit(c) && !sets_shared(c) &&
-                       adj_march_wins(c->dtype == DIRAC_C64, (int)c->nx, (int)c->ny, (int)c->nz);
+    const bool march = work && adjoint_on_march(c, n);
     hipStream_t s = (hipStream_t)stream;
     rc = upload_tables(c, s);
     if (rc) return rc;

@@ -289,10 +289,17 @@ class Lattice:
                                       _stream_handle()), self._ctx)
         return lam
 
+    def adjoint_uses_work(self, n: int) -> bool:
+        """Whether adjoint_vz over n steps is faster with work tensors (dirac_adjoint_uses_work)."""
+        uses = ctypes.c_int()
+        check(lib().dirac_adjoint_uses_work(self._ctx, int(n), ctypes.byref(uses)), self._ctx)
+        return bool(uses.value)
+
     def adjoint_vz(self, n: int, lam, work=None):
         """Backward through n steps from the current (final) state; see dirac_adjoint_vz.
-        work: 8 tensors like lam whose contents are lost; with them a step takes one
-        launch (dirac_adjoint_vz_work)."""
+        work: 8 tensors like lam whose contents are lost, none of them part of lam or
+        the state; with them a step takes one launch where adjoint_uses_work(n)
+        (dirac_adjoint_vz_work)."""
         dvi = torch.zeros(self.nz, dtype=torch.float64, device=self.device)
         dvh = torch.zeros(self.nz, dtype=torch.float64, device=self.device)
         check(lib().dirac_adjoint_vz_work(self._ctx, int(n), ptr_array([t.data_ptr() for t in lam]),
