@@ -130,23 +130,28 @@ int upload_tables(dirac_ctx *c, hipStream_t s) {
         HIPCHK(c, hipMemcpyAsync(scratch_at(c, off_tab(c) + align256(half)), c->tab_host64.data() + 4 * nz * 4,
                                  half, hipMemcpyHostToDevice, s));
     } else {
-        // theta goes up in the entries' place and becomes the entry there: the
-        // unit-modulus search took the host 1 us an entry (256 planes: 2.2 ms of a
-        // first step)
+        // The unit-modulus search takes the host 1 us an entry (256 planes: 2.0 ms of a
+        // first step) and the device 20 whatever their number, twice.  So up to six planes
+        // (2D: one) the host forms the entries; beyond, theta goes up in their place and
+        // becomes the entry there.  set_potential and a step, host / device: one plane 56 /
+        // 97 us, four 80 / 99, eight 110 / 99.
+        const bool on_host = nz <= 6;
         c->tab_host64.assign((size_t)2 * 4 * nz * 2, 0.0);
         for (int dir = 0; dir < 2; ++dir)
             for (int q = 0; q < 4; ++q)
                 for (int64_t k = 0; k < nz; ++k) {
-                    const double th = theta_of(c, q, k), thi = theta_im_of(c, q, k);
+                    const double sg = dir == 0 ? 1.0 : -1.0;
+                    const double th[2] = {sg * theta_of(c, q, k), sg * theta_im_of(c, q, k)};
                     double *e = &c->tab_host64[(((size_t)dir * 4 + q) * nz + k) * 2];
-                    e[0] = dir == 0 ? th : -th;
-                    e[1] = dir == 0 ? thi : -thi;
+                    float entry[4];
+                    if (on_host) cayley32c(th[0], th[1], entry);
+                    memcpy(e, on_host ? (const void *)entry : (const void *)th, 16);
                 }
         const size_t half = tab_bytes<float>(c);
         for (int dir = 0; dir < 2; ++dir) {
             void *t = scratch_at(c, off_tab(c) + dir * align256(half));
             HIPCHK(c, hipMemcpyAsync(t, c->tab_host64.data() + (size_t)dir * 4 * nz * 2, half, hipMemcpyHostToDevice, s));
-            HIPCHK(c, launch_table32(t, 4 * nz, s));
+            if (!on_host) HIPCHK(c, launch_table32(t, 4 * nz, s));
         }
     }
     // the host staging vectors stay alive in the context until the next upload
