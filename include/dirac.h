@@ -314,10 +314,11 @@ int dirac_set_kernel(dirac_ctx *ctx, int kernel, int tile_y, int zchunk);
  * chunks=5; 1 x fused".  split: two half-step launches in place; half: one of them;
  * fused, fused2: one or two steps in a march through LDS; tile2: 2D register tiles;
  * march3r: 3D register march (rows per thread, waves).  A functional that takes a
- * launch of its own is not listed.  For tests and timing tools; the words may
- * change.  Makes no launch.  DIRAC_E_ARG for a null argument, n < 0 (step_norm: n <
- * 1) or another call; DIRAC_E_SHAPE where the text does not fit; DIRAC_E_STATE for a
- * batch context.
+ * launch of its own is not listed.  For a batch context DIRAC_CALL_STEP tells what
+ * dirac_batch_run launches in mode 1 (tile2, most steps of a pass; march: row marches).
+ * For tests and timing tools; the words may change.  Makes no launch.  DIRAC_E_ARG for
+ * a null argument, n < 0 (step_norm: n < 1) or another call; DIRAC_E_SHAPE where the
+ * text does not fit; DIRAC_E_STATE for another call of a batch.
  */
 enum dirac_call { DIRAC_CALL_STEP = 0, DIRAC_CALL_REVERSE = 1, DIRAC_CALL_STEP_NORM = 2 };
 int dirac_route(dirac_ctx *ctx, int64_t n, int call, char *out, size_t len);
@@ -493,7 +494,8 @@ int dirac_batch_bind(dirac_ctx *ctx, void *const state[], void *const partner[],
  * steps with a per-lattice barrier between passes; mode 1: one launch per pass
  * over all lattices (both replayed from a captured HIP graph when use_graph !=
  * 0).  In mode 1, unless the tuner chose otherwise, a pass advances up to 8 steps
- * on register tiles; with a tuned march candidate, and in mode 0, one step or,
+ * on register tiles; with a tuned march candidate, untuned where every lattice is
+ * a few very long rows, and in mode 0, one step or,
  * with a two-step march (even nx for complex64), two, an odd remainder then
  * taking one one-step pass.  dirac_current tells which buffers hold the state;
  * untuned, the ones that two-step marches would leave it in.  Mode 0

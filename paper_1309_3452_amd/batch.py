@@ -91,8 +91,15 @@ class BatchedLattices:
         return self.bufs[self.current][b]
 
     def run(self, n, mode=1, graph=False):
-        """mode 1: one launch per step; mode 0: one persistent launch.  graph: replay a captured HIP graph."""
+        """mode 1: one launch per pass of up to 8 steps (see route); mode 0: one persistent
+        launch.  graph: replay a captured HIP graph."""
         check(lib().dirac_batch_run(self._ctx, int(n), int(mode), 1 if graph else 0, _stream_handle()), self._ctx)
+
+    def route(self, n) -> str:
+        """The kernels that run(n) would launch in mode 1 (dirac_route)."""
+        text = ctypes.create_string_buffer(256)
+        check(lib().dirac_route(self._ctx, int(n), 0, text, len(text)), self._ctx)
+        return text.value.decode()
 
     def norms(self):
         out = (ctypes.c_double * (3 * self.count))()

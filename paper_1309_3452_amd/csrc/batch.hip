@@ -445,6 +445,38 @@ void plan_tiles(const dirac_ctx *c, int64_t n, BRun *r) {
     r->shape = tile2_best_shape(r->ring, c->count, c->bnx.data(), c->bny.data(), fp32, tile2_kind(true, false), &us);
 }
 
+// The choice of an untuned mode 1: register tiles, unless every lattice is a few very
+// long rows (at most 8) and they fill more than a round and a half of tiles.  Then a
+// region is mostly empty, and an estimate of the passes is compared with one of the
+// default march's: a cell takes 22 ps (complex64) or 42 in its one step, 70 or 140 in its
+// two.  Forty lattices of 20000 x 1, tiles / march: complex64 one step 106 / 49 us, ten 408
+// / 331, complex128 182 / 58 and 851 / 654; fifty of 1024 x 8 complex64, one step 26 / 40.
+int default_choice(const dirac_ctx *c, int64_t n) {
+    double cells = 0.0;
+    for (int64_t b = 0; b < c->count; ++b) {
+        if (c->bny[(size_t)b] > 8) return kTileCand;
+        cells += (double)c->bnx[(size_t)b] * (double)c->bny[(size_t)b];
+    }
+    const bool fp32 = c->dtype == DIRAC_C64;
+    BRun run{kTileCand, 0, 0, 0, 0};
+    plan_tiles(c, n, &run);
+    int64_t tiles = 0;
+    for (int64_t b = 0; b < c->count; ++b) tiles += tile2_tiles(run.shape, run.ring, c->bnx[(size_t)b], c->bny[(size_t)b]);
+    if (2 * tiles <= 3 * (int64_t)resident_per_round() || run.passes == 0) return kTileCand;
+    const int kind = tile2_kind(true, false);
+    const double tile_us = (double)run.passes * (tile2_pass_us(run.shape, run.ring, tiles, cells, fp32, kind) +
+                                                 tile2_region_us((double)tiles * tile2_rows(run.shape) * 64.0, fp32, kind));
+    const double one = 5.0 + 1e-6 * cells * (fp32 ? 22.0 : 42.0), two = 5.0 + 1e-6 * cells * (fp32 ? 70.0 : 140.0);
+    const double march_us = two_step_ok(c) ? (double)(n / 2) * two + (double)(n & 1) * one : (double)n * one;
+    return tile_us <= march_us ? kTileCand : kDefaultCand;
+}
+
+// The choice a run of n steps takes.
+int choice_of(const dirac_ctx *c, int64_t n, int mode) {
+    if (c->tune_choice >= 0) return mode == 1 ? (c->tune_choice & 0xff) : (c->tune_choice >> 8);
+    return mode == 1 ? default_choice(c, n) : kDefaultCand;
+}
+
 // Upload lattice descriptors and the item list of choice q for n steps.
 int upload_batch(dirac_ctx *c, int q, int64_t n, hipStream_t s, BRun *run) {
     const BLayout Ly = blayout(c);
@@ -731,6 +763,31 @@ void cache_store(const char *path, const std::string &key, const int v[2]) {
 
 }  // namespace
 
+std::string batch_route_text(const dirac_ctx *c, int64_t n) {
+    const int q = choice_of(c, n, 1);
+    std::string t;
+    char b[96];
+    auto add = [&t](int64_t count, const char *what) {
+        if (count > 0) t += (t.empty() ? "" : "; ") + std::to_string((long long)count) + " x " + what;
+    };
+    if (q == kTileCand) {
+        BRun run{q, 0, 0, 0, 0};
+        plan_tiles(c, n, &run);
+        snprintf(b, sizeof b, "tile2 steps=%d rows=%d", run.ring, tile2_rows(run.shape));
+        add(run.passes, b);
+        return t;
+    }
+    const Cand k = kCands[q];
+    const int spp = k.spp == 2 && two_step_ok(c) ? 2 : 1;
+    if (spp == 2) {
+        snprintf(b, sizeof b, "march steps=2 width=%d rows=%d", k.txb, k.ly);
+        add(n / 2, b);
+    }
+    snprintf(b, sizeof b, "march steps=1 width=%d rows=%d", k.txb, k.ly);
+    add(spp == 2 ? n & 1 : n, b);
+    return t;
+}
+
 extern "C" {
 
 int dirac_batch_create_dt(dirac_ctx **out, int64_t count, const int64_t *nx, const int64_t *ny, int dtype,
@@ -801,8 +858,7 @@ int dirac_batch_run(dirac_ctx *c, int64_t n, int mode, int use_graph, void *stre
     if (!c->bound) return bfail(c, DIRAC_E_STATE, "nothing bound (dirac_batch_bind)");
     if (n < 0 || n > (1LL << 30) || (mode != 0 && mode != 1)) return bfail(c, DIRAC_E_ARG, "bad n or mode");
     hipStream_t s = (hipStream_t)stream;
-    const int q = c->tune_choice >= 0 ? (mode == 1 ? (c->tune_choice & 0xff) : (c->tune_choice >> 8))
-                                       : (mode == 1 ? kTileCand : kDefaultCand);
+    const int q = choice_of(c, n, mode);
     if (!use_graph) {
         drop_graph(c);
         BRun run;

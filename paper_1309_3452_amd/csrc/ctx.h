@@ -59,3 +59,6 @@ struct dirac_ctx {
     int64_t graph_flips = 0;      // ping-pong launches in the captured graph
     hipStream_t graph_stream = nullptr;
 };
+
+// The launches of dirac_batch_run's mode 1 over n steps, as dirac_route writes them.
+std::string batch_route_text(const dirac_ctx *c, int64_t n);

@@ -1078,10 +1078,12 @@ int dirac_step_norm(dirac_ctx *c, int64_t n, void *dev_out, void *stream) {
 int dirac_route(dirac_ctx *c, int64_t n, int call, char *out, size_t len) {
     if (!c || !out || len == 0) return DIRAC_E_ARG;
     out[0] = 0;
-    if (c->is_batch) return fail(c, DIRAC_E_STATE, "batch context");
+    if (c->is_batch && call != DIRAC_CALL_STEP) return fail(c, DIRAC_E_STATE, "batch context");
     if (n < 0 || call < DIRAC_CALL_STEP || call > DIRAC_CALL_STEP_NORM || (call == DIRAC_CALL_STEP_NORM && n < 1))
         return fail(c, DIRAC_E_ARG, "bad n or call");
-    const std::string t = c->dtype == DIRAC_C64 ? route_text<float>(c, n, (Op)call) : route_text<double>(c, n, (Op)call);
+    const std::string t = c->is_batch             ? batch_route_text(c, n)
+                          : c->dtype == DIRAC_C64 ? route_text<float>(c, n, (Op)call)
+                                                  : route_text<double>(c, n, (Op)call);
     if (t.size() >= len) return fail(c, DIRAC_E_SHAPE, "the text takes %zu bytes", t.size() + 1);
     memcpy(out, t.c_str(), t.size() + 1);
     return DIRAC_OK;

@@ -109,14 +109,7 @@ int64_t tile2_passes(int64_t n, int parity, int64_t count, const int64_t *nx, co
     return best;
 }
 
-// tile2_pass_us is for tiles that are mostly lattice.  Where a region is mostly ring or
-// periodic images (a few very long rows), forming its registers counts too: 1.4 ps a
-// region cell in complex64 without a potential, 1.5 in complex128, twice and four times
-// that with records, 2 and 5.6 ps with links.  Measured / estimated, one step: 400000 x 1
-// complex64 29 / 30 us, complex128 per site 76 / 76, with links 88 / 88, 400000 x 8 complex64
-// 52 / 54.
 double tile2_total_us(int64_t n, int64_t passes, int64_t nx, int64_t ny, bool fp32, int kind) {
-    constexpr double ps[2][4] = {{1.5, 5.5, 5.6, 9.0}, {1.4, 2.8, 2.0, 3.0}};
     double total = 0.0;
     for (int more = 0; more < 2; ++more) {
         const int64_t count = more ? n % passes : passes - n % passes;
@@ -125,7 +118,7 @@ double tile2_total_us(int64_t n, int64_t passes, int64_t nx, int64_t ny, bool fp
         double us = 0.0;
         const int shape = tile2_best_shape(steps, 1, &nx, &ny, fp32, kind, &us);
         const double cells = (double)tile2_tiles(shape, steps, nx, ny) * tile2_rows(shape) * 64.0;
-        total += (double)count * (us + 1e-6 * ps[fp32 ? 1 : 0][kind] * cells);
+        total += (double)count * (us + tile2_region_us(cells, fp32, kind));
     }
     return total;
 }

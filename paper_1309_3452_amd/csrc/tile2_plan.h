@@ -16,8 +16,17 @@ int64_t tile2_tiles(int shape, int ring, int64_t nx, int64_t ny);
 double tile2_pass_us(int shape, int steps, int64_t tiles, double cells, bool fp32, int kind);
 // the fastest shape for a pass of `steps` over `count` lattices, and its time
 int tile2_best_shape(int steps, int64_t count, const int64_t *nx, const int64_t *ny, bool fp32, int kind, double *us);
-// estimated microseconds of n steps in that many passes, the loads of whole regions
-// counted (see tile2.hip)
+// What forming the registers of that many region cells adds to a pass.  tile2_pass_us is
+// for tiles that are mostly lattice; where a region is mostly ring or periodic images (a
+// few very long rows) its loads count too: 1.4 ps a region cell in complex64 without a
+// potential, 1.5 in complex128, two and four times that with records, 2 and 5.6 ps with
+// links.  Measured / estimated, one step: 400000 x 1 complex64 29 / 30 us, complex128 per
+// site 76 / 76, with links 88 / 88, 400000 x 8 complex64 52 / 54.
+inline double tile2_region_us(double region_cells, bool fp32, int kind) {
+    constexpr double ps[2][4] = {{1.5, 5.5, 5.6, 9.0}, {1.4, 2.8, 2.0, 3.0}};
+    return 1e-6 * ps[fp32 ? 1 : 0][kind] * region_cells;
+}
+// estimated microseconds of n steps in that many passes, those loads counted
 double tile2_total_us(int64_t n, int64_t passes, int64_t nx, int64_t ny, bool fp32, int kind);
 // passes for n steps with the parity of `parity`; 0 if there is no such split
 int64_t tile2_passes(int64_t n, int parity, int64_t count, const int64_t *nx, const int64_t *ny, bool fp32, int kind);

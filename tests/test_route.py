@@ -133,3 +133,23 @@ def test_one_step_launches_are_priced_as_what_runs():
     kernel, whose time and not the register march's decides against threes."""
     assert route((40, 135, 81), C64, 11).startswith("3 x march3r steps=3 ")      # 149 -> 138 us
     assert route((24, 305, 284), C64, 11).startswith("3 x march3r steps=3 ")     # 729 -> 641 us
+
+
+def batch_route(sizes, dtype, n):
+    L, c, count = _abi.lib(), ctypes.c_void_p(), len(sizes)
+    nx, ny = ((ctypes.c_int64 * count)(*[s[q] for s in sizes]) for q in (0, 1))
+    assert L.dirac_batch_create(ctypes.byref(c), count, nx, ny, dtype, 0.5, 0) == 0
+    text = ctypes.create_string_buffer(256)
+    assert L.dirac_route(c, n, STEP_NORM, text, 256) == -6
+    assert L.dirac_route(c, n, STEP, text, 256) == 0
+    L.dirac_destroy(c)
+    return text.value.decode()
+
+
+def test_batches_of_a_few_long_rows_leave_the_tiles():
+    for dtype in (C64, C128):
+        assert batch_route([(20000, 1)] * 40, dtype, 1) == "1 x march steps=1 width=128 rows=64"
+        assert batch_route([(20000, 1)] * 40, dtype, 3).startswith("1 x march steps=2 width=128 rows=64; 1 x march")
+        for sizes in ([(512, 512)] * 15, [(20000, 1)] * 40 + [(64, 64)], [(8, 1024)] * 50, [(500, 1)] * 9):
+            assert "tile2" in batch_route(sizes, dtype, 10), sizes
+    assert "tile2" in batch_route([(1024, 8)] * 50, C64, 1)
