@@ -426,13 +426,7 @@ bool two_step_ok(const dirac_ctx *c) {
     return true;
 }
 
-// What a run of n steps by choice q launches: the item count and, for the
-// register tile, its passes, shape and ring.
-struct BRun {
-    int q;
-    int64_t nitems, passes;
-    int shape, ring;
-};
+using BRun = BatchRun;
 
 // The tile passes of n steps leave the state in the set where two-step marches
 // (one-step ones where they do not apply) would: the same parity of launches.
@@ -676,10 +670,12 @@ int check_abort(dirac_ctx *c, int q, int64_t n, hipStream_t s) {
 }
 
 void drop_graph(dirac_ctx *c) {
-    if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
-    if (c->graph) (void)hipGraphDestroy(c->graph);
-    c->graph_exec = nullptr;
-    c->graph = nullptr;
+    for (int p = 0; p < 2; ++p) {
+        if (c->graph_exec[p]) (void)hipGraphExecDestroy(c->graph_exec[p]);
+        if (c->graph[p]) (void)hipGraphDestroy(c->graph[p]);
+        c->graph_exec[p] = nullptr;
+        c->graph[p] = nullptr;
+    }
     c->graph_n = -1;
 }
 
@@ -858,9 +854,9 @@ int dirac_batch_run(dirac_ctx *c, int64_t n, int mode, int use_graph, void *stre
     if (!c->bound) return bfail(c, DIRAC_E_STATE, "nothing bound (dirac_batch_bind)");
     if (n < 0 || n > (1LL << 30) || (mode != 0 && mode != 1)) return bfail(c, DIRAC_E_ARG, "bad n or mode");
     hipStream_t s = (hipStream_t)stream;
-    const int q = choice_of(c, n, mode);
     if (!use_graph) {
         drop_graph(c);
+        const int q = choice_of(c, n, mode);
         BRun run;
         int rc = upload_batch(c, q, n, s, &run);
         if (rc) return rc;
@@ -873,20 +869,29 @@ int dirac_batch_run(dirac_ctx *c, int64_t n, int mode, int use_graph, void *stre
         }
         if (flips & 1) c->cur = 1 - c->cur;
     } else {
-        if (!(c->graph_exec && c->graph_n == n && c->graph_mode == (mode | (q << 4)) && c->graph_cur == c->cur)) {
+        // One graph per buffer set that holds the state: an odd number of launches
+        // alternates between them.  Both read the same list, whose choice follows from n,
+        // the mode and the tuner's.
+        if (c->graph_n != n || c->graph_mode != mode || c->graph_tune != c->tune_choice) {
             drop_graph(c);
+            const int q = choice_of(c, n, mode);
             if (!c->graph_stream) BCHK(c, hipStreamCreateWithFlags(&c->graph_stream, hipStreamNonBlocking));
             // on the caller's stream: after the earlier runs that still read the list
-            BRun run;
-            int rc = upload_batch(c, q, n, s, &run);
+            int rc = upload_batch(c, q, n, s, &c->graph_run);
             if (rc) return rc;
             if (mode == 0) {
                 rc = prepare_mode0(c, q, n, c->graph_stream);
                 if (rc) return rc;
             }
+            c->graph_n = n;
+            c->graph_mode = mode;
+            c->graph_tune = c->tune_choice;
+        }
+        const int p = c->cur;
+        if (!c->graph_exec[p]) {
             BCHK(c, hipStreamBeginCapture(c->graph_stream, hipStreamCaptureModeRelaxed));
             int64_t flips = 0;
-            rc = enqueue(c, run, n, mode, c->cur, c->graph_stream, &flips);
+            const int rc = enqueue(c, c->graph_run, n, mode, p, c->graph_stream, &flips);
             c->graph_flips = flips;
             hipGraph_t g = nullptr;
             hipError_t e = hipStreamEndCapture(c->graph_stream, &g);
@@ -895,15 +900,16 @@ int dirac_batch_run(dirac_ctx *c, int64_t n, int mode, int use_graph, void *stre
                 return rc;
             }
             if (e != hipSuccess) return bfail(c, DIRAC_E_HIP, "graph capture failed: %s", hipGetErrorString(e));
-            c->graph = g;
-            BCHK(c, hipGraphInstantiate(&c->graph_exec, c->graph, nullptr, nullptr, 0));
-            c->graph_n = n;
-            c->graph_mode = mode | (q << 4);
-            c->graph_cur = c->cur;
+            c->graph[p] = g;
+            e = hipGraphInstantiate(&c->graph_exec[p], g, nullptr, nullptr, 0);
+            if (e != hipSuccess) {
+                drop_graph(c);
+                return bfail(c, DIRAC_E_HIP, "graph instantiation failed: %s", hipGetErrorString(e));
+            }
         }
-        BCHK(c, hipGraphLaunch(c->graph_exec, s));
+        BCHK(c, hipGraphLaunch(c->graph_exec[p], s));
         if (mode == 0) {
-            int rc = check_abort(c, q, n, s);
+            int rc = check_abort(c, c->graph_run.q, n, s);
             if (rc) return rc;
         }
         if (c->graph_flips & 1) c->cur = 1 - c->cur;

@@ -7,6 +7,14 @@
 #include <string>
 #include <vector>
 
+// What a batch run of some steps by choice q launches: the item count and, for the
+// register tile, its passes, shape and ring.
+struct BatchRun {
+    int q = 0;
+    int64_t nitems = 0, passes = 0;
+    int shape = 0, ring = 0;
+};
+
 struct dirac_ctx {
     // lattice
     int ndim = 3;
@@ -51,12 +59,12 @@ struct dirac_ctx {
     std::vector<void *> bstate, bpartner, btheta;
     size_t batch_scratch_need = 0;
     int tune_choice = -1;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t graph_exec = nullptr;
-    int64_t graph_n = -1;
-    int graph_mode = -1;
-    int graph_cur = -1;
-    int64_t graph_flips = 0;      // ping-pong launches in the captured graph
+    hipGraph_t graph[2] = {};             // by the buffer set that holds the state before the run
+    hipGraphExec_t graph_exec[2] = {};
+    int64_t graph_n = -1;                 // what they were captured for: steps, mode, the tuner's choice
+    int graph_mode = -1, graph_tune = -1;
+    BatchRun graph_run;
+    int64_t graph_flips = 0;              // ping-pong launches in a captured graph
     hipStream_t graph_stream = nullptr;
 };
 

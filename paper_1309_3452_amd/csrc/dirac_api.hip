@@ -743,8 +743,10 @@ int dirac_create(dirac_ctx **out, int ndim, int64_t nx, int64_t ny, int64_t nz, 
 
 void dirac_destroy(dirac_ctx *c) {
     if (!c) return;
-    if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
-    if (c->graph) (void)hipGraphDestroy(c->graph);
+    for (int p = 0; p < 2; ++p) {
+        if (c->graph_exec[p]) (void)hipGraphExecDestroy(c->graph_exec[p]);
+        if (c->graph[p]) (void)hipGraphDestroy(c->graph[p]);
+    }
     delete c;
 }
 

@@ -1,5 +1,6 @@
 """Batches of a few very long rows: the march that the estimate picks there, graphs and
-changing step counts included, bit for bit the split kernels on each lattice."""
+changing and repeated step counts included (an odd number of launches alternates
+between the buffer sets, each with its captured graph), bit for bit the split kernels on each lattice."""
 import pytest
 import torch
 
@@ -19,7 +20,7 @@ def test_long_rows_bitwise_equal_split(dtype, graph):
                  state=[rnd(1 + b % 2, 20000 + 2 * b, dtype) for _ in range(4)]) for b in range(30)]
     batch = P.BatchedLattices(lats, dtype=dtype, dt=workloads.DT2)
     total, routes = 0, set()
-    for n in (1, 3, 12, 2, 1):
+    for n in (1, 3, 3, 3, 3, 12, 2, 1, 1, 1):
         r = batch.route(n)
         routes.add("tile2" if "tile2" in r else "march")
         batch.run(n, mode=1, graph=graph)
