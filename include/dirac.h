@@ -96,11 +96,13 @@ enum dirac_status {
 
 /* step kernels (dirac_set_kernel) */
 enum dirac_kernel {
-    DIRAC_KERNEL_AUTO = 0,   /* the fastest: 2D register tiles (up to 8 steps per
-                                launch), 3D the register march (up to 3) or, for
-                                complex64 V(z) tables of even nx, FUSED2; as many
-                                launches (mod 2) as FUSED2 where it applies, else
-                                FUSED, would make                                   */
+    DIRAC_KERNEL_AUTO = 0,   /* the fastest by estimate: 2D register tiles (up to 8
+                                steps per launch) except on a few very long rows, 3D
+                                the register march (up to 3) or FUSED2 (large
+                                complex64 boxes of even nx, complex128 tables of at
+                                most 16 columns); as many launches (mod 2) as FUSED2
+                                where it applies, else FUSED, would make
+                                (dirac_route tells the choice)                      */
     DIRAC_KERNEL_SPLIT = 1,  /* one launch per half-step, in place                 */
     DIRAC_KERNEL_FUSED = 2,  /* one launch per step, ping-pong between the buffers */
     DIRAC_KERNEL_FUSED2 = 3  /* one launch per two steps (3D: V(z) tables or
@@ -138,8 +140,10 @@ const char *dirac_last_error(const dirac_ctx *ctx);
  * Bind the state: the staggered amplitudes of Sect. 2 (A, B on sheet n-1/2,
  * C, D on sheet n; Fig. 1) or Sect. 3 (u, v).  buf0 and buf1 each give 8 (3D)
  * or 4 (2D) device arrays of nx*ny*nz amplitudes in the layout above.  buf0
- * holds the initial state; buf1 is the partner the fused kernel writes into
- * (it may alias nothing the caller still needs).  The current state flips
+ * holds the initial state; buf1 is the partner the launches of several steps write
+ * into, reversed and zero-boundary steps and the adjoint with work arrays included
+ * (it may alias nothing the caller still needs; sets that overlap each other step in
+ * place where that is possible).  The current state flips
  * between them as fused steps run; dirac_current() says where it is.  The
  * arrays stay caller-owned and must outlive their use; DIRAC_E_ARG for null
  * pointers.  No HIP call.
@@ -304,8 +308,8 @@ int dirac_coef_from_fields(void *coef, int dtype, double dt, double sgn_m, const
  *           kernels (default: chosen per kernel and lattice from the number of
  *           workgroups the device runs at once and each chunk's pipeline fill)
  * The two-step kernel uses 64 x 8 tiles (complex64) or 32 x 8 (complex128).
- * Every kernel gives the same bits.  With AUTO a tile_y or zchunk takes FUSED2 or FUSED.  The
- * adjoint uses its own in-place sweeps. */
+ * Every kernel gives the same bits.  With AUTO a zchunk, in 3D (z-slabs apart) a
+ * tile_y too, takes FUSED2 or FUSED.  The adjoint has kernels of its own. */
 int dirac_set_kernel(dirac_ctx *ctx, int kernel, int tile_y, int zchunk);
 
 /*
@@ -439,7 +443,7 @@ int dirac_adjoint_vz_work(dirac_ctx *ctx, int64_t n, void *const lam[], void *co
 
 /* *uses = 1 if dirac_adjoint_vz_work over n steps would use work arrays (the lattice is
  * large enough to gain, its state bound and n >= 2), else 0: a caller need not allocate
- * them then.  Makes no HIP call; DIRAC_E_ARG for null arguments. */
+ * them then.  Makes no launch; DIRAC_E_ARG for null arguments. */
 int dirac_adjoint_uses_work(const dirac_ctx *ctx, int64_t n, int *uses);
 
 /* The gradient of the region probability L = sum_{z_s >= z0} |psi_s|^2 after n
@@ -524,8 +528,10 @@ int dirac_batch_norms(dirac_ctx *ctx, double *out, void *stream);
  * skipped, the choice is still made, stored and written to chosen_out, and the
  * call returns DIRAC_E_STATE: the bound state is no longer valid (reload it).
  * cache_path: JSON file consulted first and updated (NULL = no cache), keyed
- * by device architecture, dtype and batch shape.  The choice is kept in the
- * context.  Synchronous.  chosen_out (may be NULL) receives
+ * by device architecture, dtype and batch shape.  A choice found there is taken as
+ * it is, also one stored when there were fewer candidates (a file from before the
+ * register tiles keeps a march: remove its entry to choose anew).  The choice is
+ * kept in the context.  Synchronous.  chosen_out (may be NULL) receives
  * (candidate for mode 1) | (candidate for mode 0) << 8.
  */
 int dirac_batch_autotune(dirac_ctx *ctx, const char *cache_path, int *chosen_out, void *stream);

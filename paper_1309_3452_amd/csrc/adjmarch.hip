@@ -284,7 +284,7 @@ int adj_march_tiles(int nx, int ny) {
 // rows), the sweeps move psi and lam three times at 5.6 (6.3) TB/s out of the caches
 // and 4.8 (4.0) from HBM.  Measured per backward step, in place / march: complex128
 // 64^3 40 / 46 us, 96^3 126 / 109, 128^3 308 / 287, 200 x 168 x 152 890 / 604, 256^3
-// 2560 / 1861; complex64 64^3 23 / 32, 128^3 127 / 158 (three tiles of 62 for 128
+// 2560 / 1861; complex64 64^3 23 / 32, 128^3 127 / 158 (three tiles of 56 for 128
 // columns), 200 x 168 x 152 548 / 315, 256^3 1546 / 1029.
 bool adj_march_wins(bool fp32, int nx, int ny, int nz) {
     const int tw = adj_width(nx), th = fp32 ? kAdjRows : kAdjRows64;

@@ -20,10 +20,14 @@
 // region is larger than the lattice) or, with zero values outside, stay zero.
 //
 // What bounds it: on small lattices the launch (about 3 us) and the latency of a
-// half-step (0.35 us with 16 rows per workgroup), on large ones the vector ALUs,
-// 18 (complex64) instructions per update over the whole region, next to the
-// bytes of one read and one write of the state per pass.  Per step, measured
-// next to the row marches (one or two steps per pass) on one box:
+// half-step (0.35 us with 16 rows per workgroup).  On large ones neither the vector ALUs
+// nor the bus alone: a workgroup loads, steps and stores one after the other, and two on
+// a CU hide little of that.  By the counters a pass of 1024 x 512 complex64 per site issues
+// vector instructions for 9.2 of its 18 us, of 2047 x 1531 for 51 of 80 (its bytes take 53),
+// of 15 lattices of 6.4 M cells together for 130 of 180.  A region cell takes 77
+// instructions a step (complex64 per site), 72 of them the update, shifts between lanes
+// being folded into it; with the rim that is 142 per cell of the lattice.  Per step,
+// measured next to the row marches (one or two steps per pass) on one box:
 //   128 x 128 complex128, no potential     1.17 us (7 steps per pass)  5.2 us
 //   512 x 512 complex64, per site          2.15 us (5)                 9.6 us
 //   1024 x 512 complex64, per site         3.50 us (5)                10.3 us
